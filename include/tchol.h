@@ -94,7 +94,9 @@ typedef struct tchol_opts {
                           tchol_factor_solve, TCHOL_OP_FACTOR_SOLVE (opts.subst
                           = 0); for tchol_solve_mixed, TCHOL_OP_MIXED_FACTOR), or NULL:
                           {claim, start} and {end} wall clock (100 MHz),
-                          {task, part | wg<<32}                                  */
+                          {task, part | wg<<32}.  A traced launch runs the plan
+                          that the query describes; without a trace a factorization
+                          may run at smaller tiles than nb                       */
   int64_t trace_words; /* length of trace in uint64 words; with trace set, a call
                           whose launch has more than trace_words / 4 work items
                           returns -i for its opts argument i and launches nothing */
@@ -339,7 +341,11 @@ TCHOL_API const char *tchol_strerror(int32_t code);
    non-NULL: counts[0..3] = {ntask, nedge, nitem, critical-path task count};
    per task (ntask entries): kind, i, j, k, parts, initial dependency count,
    upward rank; succ_off (ntask + 1) and succ (nedge); and the claim order as
-   work items item_task / item_part (nitem).  Returns 0 or a negative code. */
+   work items item_task / item_part (nitem).  The plan is the one at the given
+   nb, which a traced launch runs; an untraced factorization whose workspace
+   (of the size tchol_workspace_bytes or tchol_factor_solve_workspace_bytes
+   gives) holds it may run at smaller tiles, with a shorter critical path.
+   Returns 0 or a negative code. */
 TCHOL_API int32_t tchol_plan_query(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed, int64_t *counts,
                          int32_t *kind, int32_t *ti, int32_t *tj, int32_t *tk, int32_t *parts,
                          int32_t *dep0, int64_t *rank, int32_t *succ_off, int32_t *succ,

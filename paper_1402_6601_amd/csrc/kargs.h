@@ -22,7 +22,7 @@ typedef struct KArgs {
   double *B;            /* solve: right-hand sides, overwritten by the solution   */
   int64_t n, nb, ld, ldb, nrhs;
   int32_t T, nitem;
-  int32_t gemm_m, gemm_n, trsm_rows, gemv_rows;
+  int32_t gemm_m, gemm_n, gemm1_m, gemm1_n, trsm_rows, gemv_rows;
   int32_t *hdr;         /* HDR_WORDS header words                                 */
   int32_t *dep;         /* per task: predecessors not yet completed               */
   int32_t *done;        /* per task: work items completed                         */
@@ -31,7 +31,9 @@ typedef struct KArgs {
   const int32_t *items; /* per ticket: task, part                                 */
   const int64_t *sys;   /* per system, SYS_WORDS words: a_off, b_off, n, nb, ld   */
   int32_t *sinfo;       /* per system: failing column (batched launches)          */
-  int32_t batched;      /* 1: a failing system stops only its own work             */
+  int32_t batched;      /* 1: a failing system stops only its own work; 2: the plan's
+                           systems are one matrix at several tile sizes, and its
+                           failure (in the first one's sinfo) stops the work of all */
   int32_t nsys;
   double *D;            /* mixed precision: FP64 diagonal tiles, nb x nb each, T of them */
   int32_t mixed;        /* 0: FP64; 1: mixed-precision factor, 2: its solves, 4: both
@@ -45,6 +47,9 @@ typedef struct KArgs {
                            tiles' explicit inverses (TRTRI tasks) and applies them:
                            the solve's diagonal steps (y in S) and the TRSMs (by
                            128-row blocks); 0: substitution in place          */
+  int32_t inv_rows;     /* inv: rows of a TRSM item                               */
+  int32_t finv;         /* inv: POTRF leaves L_kk^{-1} in Dinv (tiles of order <= 128),
+                           and TRTRI, for the solve, writes DinvT only            */
   double *Dinv;         /* mixed precision: L_kk^{-1}, nb x nb each (FP64); adjoint:
                            two scratch tiles per diagonal tile (Mn, Y^T)          */
   double *DinvT;        /* mixed precision, inv and adjoint: L_kk^{-T}, nb x nb each */

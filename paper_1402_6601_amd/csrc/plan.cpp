@@ -88,6 +88,7 @@ struct Builder {
 struct FactorIds {
   std::vector<int32_t> potrf, trsm;  // trsm[i * T + k]
   std::vector<int32_t> trtri;        // inverse-TRSM factorizations: TRTRI(k) for k < T-1, else -1
+  int32_t T = 0;                     // tiles per side
 };
 
 // The mixed-precision factorization (OP_FACTOR_INV) has its own costs: its
@@ -125,6 +126,24 @@ int64_t weight(int32_t kind, int32_t op) {
   }
 }
 
+// Run plans by small tiles: the time of one work item of a task in us (claim
+// and publication included), from traces at tiles of 128 and 64 (the
+// solve's at its own tiles).  The items of a task run side by side, so this is
+// both the task's step on the critical path and the cost of each item.
+int64_t run_weight(const Plan& p, int64_t t) {
+  const int64_t nb = p.systems[p.sys[t]].nb;
+  switch (p.kind[t]) {
+    case TK_POTRF: return 5 + 28 * nb / 128;
+    case TK_TRSM: return p.finv ? 10 + 8 * nb / 128 : 5 + 25 * nb / 128;
+    case TK_SYRK: return 7 + 6 * nb / 128;
+    case TK_GEMM: return 7 + 6 * nb / 128;
+    case TK_GEMM2: return 12 + 32 * nb / 128;
+    case TK_TRTRI: return 5 + 34 * nb / 128;
+    case TK_FTRSV: case TK_BTRSV: return p.inv ? 6 + 2 * nb / 128 : 8 + 25 * nb / 128;
+    default: return 6 + 2 * nb / 128;
+  }
+}
+
 // Work items of the POTRF of a tile of order m in a system of several tiles
 // (on the critical path of the tile DAG).  Tiles above 128 are factored as a
 // small tile DAG over 128 x 128 sub-blocks whose sub-units the task's work
@@ -143,6 +162,8 @@ int32_t potrf_parts(int64_t m) {
 // inv_trsm: TRSM(i, k) applies L_kk^{-1} from TRTRI(k), which runs between
 // POTRF(k) and the step's TRSMs (k < T-1: every tile with a TRSM below it is
 // a full one), by 128-row blocks on the matrix cores.
+// With the plan's finv (and inv_trsm), POTRF(k) itself leaves L_kk^{-1}: no
+// TRTRI tasks, and TRSM(i, k) follows POTRF(k).
 void build_factor(Builder& b, FactorIds* ids = nullptr, bool trtri = false, bool inv_trsm = false) {
   auto& succ = b.succ;
   const int32_t T = b.T;
@@ -173,10 +194,10 @@ void build_factor(Builder& b, FactorIds* ids = nullptr, bool trtri = false, bool
     id_potrf[k] = b.add(TK_POTRF, k, k, k,
                         T > 1 ? potrf_parts(b.tile_size(k))
                               : (wgs > 1 && b.tile_size(k) > 128 ? std::min(wgs, potrf_parts(b.tile_size(k))) : 1));
-    if (inv_trsm && k + 1 < T) id_inv[k] = b.add(TK_TRTRI, k, k, k, Builder::cdiv(b.tile_size(k), b.s.trsm_rows));
+    if (inv_trsm && !b.p.finv && k + 1 < T) id_inv[k] = b.add(TK_TRTRI, k, k, k, Builder::cdiv(b.tile_size(k), b.s.trsm_rows));
     for (int32_t i = k + 1; i < T; ++i)
       id_trsm[ix2(i, k)] =
-          b.add(TK_TRSM, i, k, k, Builder::cdiv(b.tile_size(i), inv_trsm ? b.s.gemm_m : b.s.trsm_rows));
+          b.add(TK_TRSM, i, k, k, Builder::cdiv(b.tile_size(i), inv_trsm ? b.s.inv_rows : b.s.trsm_rows));
     for (int32_t i = k + 1; i < T; ++i) {
       int32_t sb = Builder::cdiv(b.tile_size(i), b.s.syrk_b);
       id_syrk[ix2(i, k)] = b.add(TK_SYRK, i, i, k, sb * (sb + 1) / 2);
@@ -184,7 +205,8 @@ void build_factor(Builder& b, FactorIds* ids = nullptr, bool trtri = false, bool
         if (pair_first(j, k)) continue;  // created with its second update, after TRSM(., k+1)
         const bool second = pair_second(j, k);
         const int32_t id = second ? b.add(TK_GEMM2, i, j, k - 1, gemm_parts(i, j))
-                                  : b.add(TK_GEMM, i, j, k, gemm_parts(i, j));
+                                  : b.add(TK_GEMM, i, j, k, Builder::cdiv(b.tile_size(i), b.s.gemm1_m) *
+                                                                Builder::cdiv(b.tile_size(j), b.s.gemm1_n));
         id_gemm[ix3(i, j, k)] = id;
         if (second) id_gemm[ix3(i, j, k - 1)] = id;
       }
@@ -221,6 +243,7 @@ void build_factor(Builder& b, FactorIds* ids = nullptr, bool trtri = false, bool
     ids->potrf = id_potrf;
     ids->trsm = id_trsm;
     ids->trtri = id_inv;
+    ids->T = T;
   }
 }
 
@@ -256,7 +279,20 @@ void build_solve(Builder& b, const FactorIds* after = nullptr, Diag diag = Diag:
   }
   for (int32_t k = 0; k < T; ++k)
     if (id_tri[k] >= 0) succ[id_tri[k]].push_back(id_ft[k]);
-  if (after) {
+  if (after && after->T != T) {
+    // a factor at smaller tiles (r to a side of this solve's): the last of a
+    // diagonal tile's POTRFs follows all of its other tasks; an off-diagonal
+    // tile is final with all of its TRSMs
+    const int32_t Tf = after->T;
+    const int32_t r = (int32_t)(b.nb / b.p.systems[0].nb);
+    for (int32_t k = 0; k < T; ++k) {
+      succ[after->potrf[std::min(Tf, (k + 1) * r) - 1]].push_back(id_tri[k] >= 0 ? id_tri[k] : id_ft[k]);
+      for (int32_t i = k + 1; i < T; ++i)
+        for (int32_t fi = i * r; fi < std::min(Tf, (i + 1) * r); ++fi)
+          for (int32_t fk = k * r; fk < (k + 1) * r; ++fk)
+            succ[after->trsm[(size_t)fi * Tf + fk]].push_back(id_fg[ix2(i, k)]);
+    }
+  } else if (after) {
     // the solve of a system reads the final tiles of its factor
     for (int32_t k = 0; k < T; ++k) {
       if (given(k) && diag == Diag::kInvHere)
@@ -398,6 +434,7 @@ std::tuple<int32_t, int32_t, int32_t, int32_t, int32_t> tie_key(const Plan& p, i
   int32_t kind = p.kind[t], step = p.tk[t];
   if (kind == TK_BTRSV || kind == TK_BGEMV) step = T + (T - 1 - p.tk[t]);
   if (p.op == TCHOL_OP_BATCHED && kind >= TK_FTRSV && kind <= TK_BGEMV) step += T;  // a system's solve after its factor
+  // (a run plan's solve tasks are a second system, after the first in this order)
   const bool adjoint = p.op == TCHOL_OP_BACKWARD;
   if (adjoint) step = T - 1 - p.tk[t];  // the adjoint runs its steps downwards
   int32_t kord = kind;
@@ -448,7 +485,7 @@ const Split& default_split() {
 const Split& split_for(int32_t op) {
   static const Split mixed = [] {
     Split s;
-    s.gemm_m = 256;
+    s.gemm_m = s.gemm1_m = 256;
     return s;
   }();
   return op == OP_FACTOR_INV ? mixed : default_split();
@@ -471,6 +508,10 @@ bool list_schedule(Plan& p, int64_t ni) {
   std::vector<double> dur(nt);
   for (int64_t t = 0; t < nt; ++t) {
     double w = (double)weight(p.kind[t], p.op);
+    if (p.run) {
+      dur[t] = (double)run_weight(p, t);
+      continue;
+    }
     if (p.op == TCHOL_OP_BATCHED) {
       const double u = (double)(p.systems[p.sys[t]].nb / 16);
       w *= u * u * u;
@@ -543,8 +584,8 @@ bool finalize(Plan& p, std::vector<std::vector<int32_t>>& succ, int32_t policy, 
   for (int64_t t = nt - 1; t >= 0; --t) {
     int64_t best = 0;
     for (int32_t e = p.succ_off[t]; e < p.succ_off[t + 1]; ++e) best = std::max(best, p.rank[p.succ[e]]);
-    int64_t w = weight(p.kind[t], p.op);
-    if (p.op == TCHOL_OP_BATCHED) {
+    int64_t w = p.run ? run_weight(p, t) : weight(p.kind[t], p.op);
+    if (p.op == TCHOL_OP_BATCHED && !p.run) {
       const int64_t u = p.systems[p.sys[t]].nb / 16;
       w *= u * u * u;
     }
@@ -604,7 +645,7 @@ bool finalize(Plan& p, std::vector<std::vector<int32_t>>& succ, int32_t policy, 
 }  // namespace
 
 std::shared_ptr<Plan> build_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed,
-                                 const Split& split) {
+                                 const Split& split, bool run) {
   auto plan = std::make_shared<Plan>();
   Plan& p = *plan;
   p.op = op;
@@ -612,6 +653,8 @@ std::shared_ptr<Plan> build_plan(int32_t op, int64_t n, int64_t nb, int32_t poli
   p.nb = nb;
   p.policy = policy;
   p.seed = seed;
+  p.run = run;
+  p.finv = run && op == OP_FACTOR_INVT;
   int64_t T64 = n == 0 ? 0 : (n + nb - 1) / nb;
   // the factorization's DAG has about T^3/6 tasks, the adjoint's T^3/3
   if (T64 > 1200 || (op == TCHOL_OP_BACKWARD && T64 > 160)) return nullptr;
@@ -645,6 +688,7 @@ std::shared_ptr<Plan> build_plan(int32_t op, int64_t n, int64_t nb, int32_t poli
   else
     return nullptr;
   p.inv = op == TCHOL_OP_SOLVE || op == OP_FACTOR_INVT;
+  p.split = split;
   if (!finalize(p, succ, policy, seed)) return nullptr;
   return plan;
 }
@@ -658,6 +702,7 @@ std::shared_ptr<Plan> build_batched_plan(const std::vector<System>& systems, int
   p.policy = policy;
   p.seed = seed;
   p.systems = systems;
+  p.split = split;
   int64_t est = 0;
   for (auto& sy : p.systems) {
     const int64_t T64 = sy.n == 0 ? 0 : (sy.n + sy.nb - 1) / sy.nb;
@@ -724,6 +769,100 @@ std::shared_ptr<const Plan> get_batched_plan(const std::vector<System>& systems,
   if (cache.size() >= 8) cache.clear();
   cache[key] = p;
   return p;
+}
+
+// The critical path of a factorization by tiles of nb is T steps of POTRF,
+// inverse, TRSM and SYRK, each a chain of dependent work items whose length
+// grows with nb, against n^3 / 3 flops shared by all workgroups.  Tiles of 128
+// have by far the shortest path (POTRF with the inverse 29 us, TRSM 6 us, SYRK
+// 7 us per 128 columns, where a 512 tile takes 790 us for its four times as
+// many), but their updates, of 128 or 256 columns, pay the work items' fixed
+// cost (load and store of the output tile) four times as often.
+constexpr int64_t kRunTile = 128;
+constexpr int64_t kRunTileOrder = 12288;
+
+int64_t run_tile(int64_t n, int64_t nb) { return nb > kRunTile && nb % kRunTile == 0 && n <= kRunTileOrder ? kRunTile : nb; }
+
+namespace {
+
+// Tiles of at most 128: the TRSMs by 32-row strips, the SYRKs and the single
+// GEMMs (the last update before a TRSM) by 64 x 64 blocks: short items, on the
+// critical path.  The double updates, which carry the work, as everywhere.
+const Split& run_split(int32_t op, int64_t nb) {
+  static const Split fine = [] {
+    Split s;
+    s.syrk_b = s.gemm1_m = s.gemm1_n = 64;
+    s.inv_rows = 32;
+    return s;
+  }();
+  return nb <= kRunTile && (op == TCHOL_OP_FACTOR || op == OP_FACTOR_INVT || op == TCHOL_OP_BATCHED) ? fine : split_for(op);
+}
+
+// The run plans, a small process-wide cache.
+template <class Make>
+std::shared_ptr<const Plan> cached_run_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed, Make make) {
+  static std::mutex mu;
+  static std::map<std::tuple<int32_t, int64_t, int64_t, int32_t, uint32_t>, std::shared_ptr<const Plan>> cache;
+  auto key = std::make_tuple(op, n, nb, policy, policy == TCHOL_POLICY_RANDOM ? seed : 0u);
+  {
+    std::lock_guard<std::mutex> g(mu);
+    auto it = cache.find(key);
+    if (it != cache.end()) return it->second;
+  }
+  std::shared_ptr<const Plan> p = make();
+  if (!p) return nullptr;
+  std::lock_guard<std::mutex> g(mu);
+  if (cache.size() > 32) cache.clear();
+  cache[key] = p;
+  return p;
+}
+
+}  // namespace
+
+std::shared_ptr<const Plan> get_run_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed) {
+  if (op != TCHOL_OP_FACTOR && op != OP_FACTOR_INVT) return get_plan(op, n, nb, policy, seed);
+  const int64_t rt = run_tile(n, nb);
+  if (rt > kRunTile) return get_plan(op, n, nb, policy, seed);
+  return cached_run_plan(op, n, rt, policy, seed, [&]() -> std::shared_ptr<const Plan> {
+    return build_plan(op, n, rt, policy, seed, run_split(op, rt), true);
+  });
+}
+
+std::shared_ptr<const Plan> get_run_merged_plan(int64_t n, int64_t nb, int32_t policy, uint32_t seed, bool inv) {
+  const int64_t rt = run_tile(n, nb);
+  std::vector<System> systems(1);
+  systems[0].n = n;
+  systems[0].nb = rt;
+  systems[0].ld = n;
+  if (rt > kRunTile) return get_batched_plan(systems, policy, seed, inv);
+  // the key's operation: with and without inverses
+  return cached_run_plan(inv ? OP_FACTOR_INVT : TCHOL_OP_FACTOR, n, nb, policy, seed, [&]() -> std::shared_ptr<const Plan> {
+    if ((n + rt - 1) / rt > 1200) return nullptr;
+    auto plan = std::make_shared<Plan>();
+    Plan& p = *plan;
+    p.op = TCHOL_OP_BATCHED;
+    p.n = n;
+    p.nb = rt;
+    p.run = true;
+    p.inv = p.finv = inv;
+    p.policy = policy;
+    p.seed = seed;
+    p.split = run_split(p.op, rt);
+    p.systems = systems;
+    if (nb != rt) {
+      p.systems.push_back(systems[0]);
+      p.systems[1].nb = nb;
+    }
+    for (auto& sy : p.systems) sy.T = (int32_t)((n + sy.nb - 1) / sy.nb);
+    std::vector<std::vector<int32_t>> succ;
+    FactorIds ids;
+    Builder f(p, p.split, succ, 0);
+    build_factor(f, &ids, false, inv);
+    Builder s(p, p.split, succ, (int32_t)p.systems.size() - 1);
+    build_solve(s, &ids, inv ? Diag::kInvHere : Diag::kSubst);
+    if (!finalize(p, succ, policy, seed)) return nullptr;
+    return plan;
+  });
 }
 
 }  // namespace tchol

@@ -32,6 +32,16 @@ struct System {
                                  // leading dimension of the FP32 matrix (d_off its offset)
 };
 
+// Work-item granularity (rows x cols of one work item of each task kind).
+struct Split {
+  int32_t gemm_m = 128, gemm_n = 128;   // GEMM2 output sub-tile (also the adjoint's products)
+  int32_t gemm1_m = 128, gemm1_n = 128;  // GEMM output sub-tile
+  int32_t syrk_b = 128;                 // SYRK output sub-tile (square; the lower ones of the tile)
+  int32_t trsm_rows = 32;               // TRSM row strip
+  int32_t inv_rows = 128;               // rows of a TRSM item that applies an explicit inverse
+  int32_t gemv_rows = 32;               // solve update row strip
+};
+
 struct Plan {
   int32_t op = 0;          // TCHOL_OP_FACTOR / TCHOL_OP_SOLVE / TCHOL_OP_BATCHED
   int64_t n = 0, nb = 0;   // matrix order, tile size (single-system plans)
@@ -39,6 +49,9 @@ struct Plan {
   int32_t policy = 0;      // TCHOL_POLICY_*
   uint32_t seed = 0;       // for TCHOL_POLICY_RANDOM
   std::vector<System> systems;             // one for factor and solve plans
+  Split split;             // the work items' sizes
+  bool run = false;        // a run plan by tiles of at most 128 (its work items cost run_weight)
+  bool finv = false;       // POTRF leaves L_kk^{-1} for the TRSMs (run plans by tiles of at most 128)
   bool inv = false;        // the FP64 solve in it applies explicit inverses of the diagonal
                            // tiles, computed by its TRTRI tasks (single-system plans)
   // per task
@@ -70,21 +83,13 @@ constexpr int32_t OP_SOLVE_SUBST = 18;
 // the factorization of the merged factor + solve launch, alone.
 constexpr int32_t OP_FACTOR_INVT = 19;
 
-// Work-item granularity (rows x cols of one work item of each task kind).
-struct Split {
-  int32_t gemm_m = 128, gemm_n = 128;   // GEMM output sub-tile (also the adjoint's products)
-  int32_t syrk_b = 128;                 // SYRK output sub-tile (square; the lower ones of the tile)
-  int32_t trsm_rows = 32;               // TRSM row strip
-  int32_t gemv_rows = 32;               // solve update row strip
-};
-
 // Builds (or fetches from a process-wide cache) the plan.  Returns nullptr
 // for arguments the planner cannot represent (task counts beyond int32).
 std::shared_ptr<const Plan> get_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed);
 
 // Uncached build, used by get_plan and by the plan-introspection entry point.
 std::shared_ptr<Plan> build_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed,
-                                 const Split& split);
+                                 const Split& split, bool run = false);
 
 // Factorization followed by the solve, for every system, as one DAG: each
 // system's factor tasks, then its solve tasks, joined by the data-flow
@@ -102,6 +107,18 @@ std::shared_ptr<Plan> build_batched_plan(const std::vector<System>& systems, int
 // part of the plan's task structure; the caller supplies them per launch).
 std::shared_ptr<const Plan> get_batched_plan(const std::vector<System>& systems, int32_t policy, uint32_t seed,
                                              bool inv = false);
+
+// The tile order a single-system launch runs with, for the caller's nb (the
+// plans above, and the plan queries, are always at the caller's).
+int64_t run_tile(int64_t n, int64_t nb);
+
+// The plans launches run: as get_plan and the merged get_batched_plan, with
+// the factorization at tiles of run_tile(n, nb) and, there, the finer work
+// items of run_split.  The merged plan's solve keeps the caller's tiles: its
+// systems are the matrix at run_tile (factor tasks) and at nb (solve tasks).
+std::shared_ptr<const Plan> get_run_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed);
+// inv as for build_batched_plan.
+std::shared_ptr<const Plan> get_run_merged_plan(int64_t n, int64_t nb, int32_t policy, uint32_t seed, bool inv);
 
 const Split& default_split();
 // The split a single-system plan of this operation is built with: the

@@ -88,11 +88,12 @@ InvLayout inv_layout(const Plan& p, int64_t nrhs) {
   InvLayout V;
   V.end = layout_of(p).end;
   if (!p.inv || p.systems.empty()) return V;
-  const tchol::System& sy = p.systems[0];
-  const int64_t T = sy.n == 0 ? 0 : (sy.n + sy.nb - 1) / sy.nb;
+  // the factorization's tiles and the solve's (the same system but in run plans)
+  const tchol::System &sf = p.systems.front(), &sy = p.systems.back();
+  auto tiles = [](const tchol::System& s) { return s.n == 0 ? 0 : (s.n + s.nb - 1) / s.nb * s.nb * s.nb; };
   V.dinvt = align_up(V.end);
-  V.dinv = align_up(V.dinvt + 8 * T * sy.nb * sy.nb);  // L_kk^{-1}, for the TRSM items
-  V.sx = align_up(V.dinv + 8 * T * sy.nb * sy.nb);
+  V.dinv = align_up(V.dinvt + 8 * tiles(sy));  // L_kk^{-1}, for the TRSM items
+  V.sx = align_up(V.dinv + 8 * tiles(sf));
   V.end = align_up(V.sx + 8 * sy.n * std::max<int64_t>(nrhs, 1));
   return V;
 }
@@ -280,12 +281,15 @@ const tchol_opts kDefaultOpts = {TCHOL_POLICY_LIST, 0u, 0, nullptr, nullptr, 0, 
 // failing columns.  mixed: 0 FP64; 1 / 2 the mixed-precision factor / solve
 // (A is then the FP32 working copy and D its FP64 diagonal tiles); 6 the
 // compact FP64 instance for batched systems of one tile each, 7 the same
-// reading and writing FP32 matrices at A32.  Returns the library code.
+// reading and writing FP32 matrices at A32.  sinfo_all false: a merged plan,
+// whose systems are one matrix (only the first one's sinfo is read).  Returns
+// the library code.
 int32_t execute(const Plan& plan, const Image& img, double* A, double* B, int64_t nrhs, bool wide, bool batched,
                 void* ws, int64_t ws_bytes, void* stream_v, const tchol_opts& o, int32_t ws_arg,
                 int32_t* sinfo_out, double* D = nullptr, int mixed = 0, double* Qp = nullptr,
                 double* LTp = nullptr, int64_t ldq = 0, double* Dinv = nullptr, double* DinvT = nullptr,
-                double* Sx = nullptr, uint16_t* H = nullptr, int64_t hrows = 0, float* A32 = nullptr) {
+                double* Sx = nullptr, uint16_t* H = nullptr, int64_t hrows = 0, float* A32 = nullptr,
+                bool sinfo_all = true) {
   const Layout& L = img.lay;
   if (ws_bytes < L.end) return -(ws_arg + 1);
   if (reinterpret_cast<uintptr_t>(ws) % kAlign != 0) return -ws_arg;
@@ -307,11 +311,14 @@ int32_t execute(const Plan& plan, const Image& img, double* A, double* B, int64_
   a.nrhs = nrhs;
   a.T = plan.T;
   a.nitem = (int32_t)plan.nitem();
-  const tchol::Split& sp = tchol::split_for(plan.op);
+  const tchol::Split& sp = plan.split;
   a.gemm_m = sp.gemm_m;
   a.gemm_n = sp.gemm_n;
+  a.gemm1_m = sp.gemm1_m;
+  a.gemm1_n = sp.gemm1_n;
   a.syrk_b = sp.syrk_b;
   a.trsm_rows = sp.trsm_rows;
+  a.inv_rows = sp.inv_rows;
   a.gemv_rows = sp.gemv_rows;
   a.hdr = reinterpret_cast<int32_t*>(w + L.hdr);
   a.dep = reinterpret_cast<int32_t*>(w + L.dep);
@@ -322,7 +329,8 @@ int32_t execute(const Plan& plan, const Image& img, double* A, double* B, int64_
   a.sys = reinterpret_cast<const int64_t*>(w + L.sys);
   a.sinfo = reinterpret_cast<int32_t*>(w + L.sinfo);
   a.pool = reinterpret_cast<int32_t*>(w + L.pool);
-  a.batched = batched ? 1 : 0;
+  const bool two_tiles = !sinfo_all && plan.systems.size() == 2;  // a run plan: one matrix at two tile sizes
+  a.batched = batched ? (two_tiles ? 2 : 1) : 0;
   a.nsys = (int32_t)plan.systems.size();
   a.D = D;
   a.mixed = mixed;
@@ -333,6 +341,8 @@ int32_t execute(const Plan& plan, const Image& img, double* A, double* B, int64_
   a.DinvT = DinvT;
   a.S = Sx;
   a.inv = plan.inv ? 1 : 0;
+  // POTRF leaves the inverses that the TRSMs apply where one workgroup factors a tile in LDS
+  a.finv = plan.inv && plan.op != TCHOL_OP_SOLVE && plan.systems[0].nb <= 128 ? 1 : 0;
   a.H = H;
   a.hrows = hrows;
   a.A32 = A32;
@@ -355,7 +365,7 @@ int32_t execute(const Plan& plan, const Image& img, double* A, double* B, int64_
                          wide ? 1 : 0, stream, ev0, ev1);
   if (e == hipSuccess) e = hipMemcpyAsync(hdr, a.hdr, sizeof(hdr), hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess && sinfo_out && a.nsys > 0)
-    e = hipMemcpyAsync(sinfo_out, a.sinfo, 4 * (size_t)a.nsys, hipMemcpyDeviceToHost, stream);
+    e = hipMemcpyAsync(sinfo_out, a.sinfo, 4 * (size_t)(two_tiles ? 1 : a.nsys), hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e == hipSuccess && o.kernel_ms) {
     float ms = 0.f;
@@ -383,8 +393,14 @@ int32_t run(int32_t op, double* A, double* B, int64_t n, int64_t nb, int64_t nrh
   const int32_t pop = op == TCHOL_OP_SOLVE && o.subst        ? tchol::OP_SOLVE_SUBST
                      : op == TCHOL_OP_FACTOR && o.inv_trsm ? tchol::OP_FACTOR_INVT
                                                            : op;
+  // a traced launch runs the plan that the queries describe, and so does one
+  // whose workspace does not hold the run plan
   auto plan = tchol::get_plan(pop, n, nb, o.policy, o.seed);
   if (!plan) return TCHOL_E_UNSUPPORTED;
+  if (!o.trace) {
+    auto rp = tchol::get_run_plan(pop, n, nb, o.policy, o.seed);
+    if (rp && ws_bytes >= inv_layout(*rp, nrhs).end) plan = rp;
+  }
   if (o.trace && o.trace_words / 4 < plan->nitem()) return -(ws_arg + 3);
   auto img = image_of(plan);
   // 16-byte panel transfers need an even leading dimension and an aligned matrix
@@ -561,6 +577,12 @@ int64_t factor_solve_bytes(int64_t n, int64_t nb, int64_t nrhs, bool inv) {
   return inv_layout(*plan, nrhs).end;
 }
 
+// The same for the plan that the launch runs when its workspace holds it.
+int64_t factor_solve_run_bytes(int64_t n, int64_t nb, int64_t nrhs, bool inv) {
+  auto plan = tchol::get_run_merged_plan(n, nb, TCHOL_POLICY_LIST, 0, inv);
+  return plan ? inv_layout(*plan, nrhs).end : 0;
+}
+
 // The merged factor + solve launch on validated arguments (n > 0).  pinned:
 // keep the plan's constant image in pinned host memory (allocated once per
 // plan); otherwise in pageable memory, so that the call allocates no device
@@ -576,7 +598,14 @@ int32_t factor_solve_run(double* A, int64_t n, int64_t nb, double* B, int64_t nr
   systems[0].n = n;
   systems[0].nb = nb;
   systems[0].ld = n;
-  auto plan = tchol::get_batched_plan(systems, o.policy, o.seed, inv);
+  // a traced launch runs the plan that the queries describe, and so does one
+  // whose workspace does not hold the run plan
+  std::shared_ptr<const Plan> plan;
+  if (!o.trace) {
+    plan = tchol::get_run_merged_plan(n, nb, o.policy, o.seed, inv);
+    if (plan && ws_bytes < inv_layout(*plan, nrhs).end) plan = nullptr;
+  }
+  if (!plan) plan = tchol::get_batched_plan(systems, o.policy, o.seed, inv);
   if (!plan) return TCHOL_E_UNSUPPORTED;
   const InvLayout V = inv_layout(*plan, nrhs);
   if (ws_bytes < V.end) return -7;
@@ -593,7 +622,9 @@ int32_t factor_solve_run(double* A, int64_t n, int64_t nb, double* B, int64_t nr
     if (it != cache.end() && !it->second.first.expired()) {
       img = it->second.second;
     } else {
-      img = make_image(*plan, pinned, &systems);
+      std::vector<tchol::System> sys = plan->systems;
+      for (auto& sy : sys) sy.ld = n;
+      img = make_image(*plan, pinned, &sys);
       if (cache.size() > 16) cache.clear();
       cache[key] = std::make_pair(std::weak_ptr<const Plan>(plan), img);
     }
@@ -605,7 +636,7 @@ int32_t factor_solve_run(double* A, int64_t n, int64_t nb, double* B, int64_t nr
   double* Dinv = plan->inv ? reinterpret_cast<double*>(w + V.dinv) : nullptr;
   double* Sx = plan->inv ? reinterpret_cast<double*>(w + V.sx) : nullptr;
   const int32_t rc = execute(*plan, *img, A, B, nrhs, wide, true, ws, ws_bytes, stream, o, 6, &info, nullptr, 0,
-                             nullptr, nullptr, 0, Dinv, DinvT, Sx);
+                             nullptr, nullptr, 0, Dinv, DinvT, Sx, nullptr, 0, nullptr, false);
   if (rc != 0) return rc;
   return info;
 }
@@ -629,6 +660,10 @@ int64_t tchol_workspace_bytes(int32_t op, int64_t n, int64_t nb, int64_t nrhs) {
     auto plain = tchol::get_plan(TCHOL_OP_FACTOR, n, nb, TCHOL_POLICY_RANK, 0);
     if (!plain) return TCHOL_E_UNSUPPORTED;
     end = std::max(end, inv_layout(*plain, nrhs).end);
+    for (int32_t rop : {tchol::OP_FACTOR_INVT, (int32_t)TCHOL_OP_FACTOR}) {
+      auto rp = tchol::get_run_plan(rop, n, nb, TCHOL_POLICY_LIST, 0);
+      if (rp) end = std::max(end, inv_layout(*rp, nrhs).end);
+    }
   }
   return end;
 }
@@ -703,7 +738,9 @@ int64_t tchol_factor_solve_workspace_bytes(int64_t n, int64_t nb, int64_t nrhs) 
   if (n < 0 || n > INT32_MAX) return -1;
   if (!nb_ok(nb)) return -2;
   if (nrhs < 0) return -3;
-  return tchol::factor_solve_bytes(n, nb, nrhs, true);
+  const int64_t need = tchol::factor_solve_bytes(n, nb, nrhs, true);
+  if (need < 0) return need;
+  return std::max({need, tchol::factor_solve_run_bytes(n, nb, nrhs, true), tchol::factor_solve_run_bytes(n, nb, nrhs, false)});
 }
 
 int32_t tchol_factor_solve(double* A, int64_t n, int64_t nb, double* B, int64_t nrhs, void* ws, int64_t ws_bytes,

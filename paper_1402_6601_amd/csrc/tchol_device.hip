@@ -154,6 +154,11 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
+// Workgroup barrier for data in LDS only: it waits for this wavefront's LDS
+// accesses, not for its global stores (__syncthreads waits for both, and a
+// write-through store takes thousands of cycles).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
+
 // ---------------------------------------------------------------------------
 // Matrix-core tile product used by every update:
 //     C[M x N] -= Ap[M x K] * Bp[N x K]^T,   M <= BM, N <= BN, K % KC == 0.
@@ -821,17 +826,6 @@ __device__ __forceinline__ void gemm_bf16x6_wide(float* __restrict__ C, int64_t 
 #define PPLD 516                              // LDS leading dimension of the panel
 #define P_STAGE_DOUBLES (272 * 8 * 4)         // stages of gemm_core<SEG, 256, 16, 8, 4, 4, 0>
 
-// ---------------------------------------------------------------------------
-// POTRF of a tile of order m <= 128 held in LDS for the whole factorization:
-// loaded once, factored right-looking by 16-column panels, stored once.  Per
-// panel: the 16 x 16 diagonal block is factored on wavefront 0 in registers
-// (diag16_x), every thread solves one row below it, and the trailing
-// lower blocks take the panel's update on the matrix cores (16 x 16 blocks,
-// K = 16); wavefront 0 updates and factors the next diagonal block first,
-// while the other wavefronts update the rest.  Returns 0, or the 1-based
-// column (within the tile) whose pivot is not positive.
-#define SLD 132   // LDS leading dimension of the resident tile
-
 // Factors the 16 x 16 (w x w, rows and columns past w padded with the
 // identity) diagonal block at (off, off) of an LDS matrix X (leading
 // dimension LDX) on one wavefront: lane r holds row r in registers, the
@@ -917,110 +911,462 @@ __device__ __forceinline__ int diag16_x(double* X, int off, int w, double* Ldd, 
   return info;
 }
 
-__device__ __forceinline__ int diag16_lds(double* As, int c0, int w, double* Ldd, double* Linv, int lane) {
-  return diag16_x<SLD, PW + 1>(As, c0, w, Ldd, Linv, lane, c0);
+// ---------------------------------------------------------------------------
+// Four columns of a 16-column panel at once.  A wavefront holds the panel's
+// diagonal block as xd in the layout of an MFMA result (element i of lane l:
+// row l % 16, column 4 i + l / 16 of the block; rows and columns past the
+// tile's order hold the identity, the strict upper triangle any finite
+// values).  Sub-step s broadcasts the 4 x 4 diagonal block of columns
+// 4 s .. 4 s + 3 (ten readlanes) and factors it redundantly in every lane,
+// with lane l also forming column l / 16 of the block's inverse W.
+// The products run on v_mfma_f64_4x4x4_4b: element s of a 16-row block is
+// the B operand of four 4 x 4 x 4 blocks (4 rows each) as it stands, and the
+// result has the same layout.  One solves four columns of a row block
+// (x[s] := x[s] W^T, W in every block of the A operand), and one more per
+// later column quad i applies them (x[i] -= x[s] Y_i^T, Y_i the solved rows
+// 4 i .. 4 i + 3 of the diagonal block, copied to every block of the A operand
+// by row rotations).  Against a 16 x 16 x 4 product per step these take 17
+// instead of 64 cycles of the matrix core, give their result after 27 instead
+// of 79, and skip the columns that are done.  The chain per four columns is
+// four pivots of a reciprocal square root, one third-order step (hardware
+// estimate to better than an ulp) and two operations each, plus two products,
+// instead of sixteen dependent pivots with a broadcast and a column update.
+// The diagonal block's products come first, since the next sub-step waits
+// for them; the row blocks' run under the next sub-step's pivots.
+// lf: the columns of L_dd (lower triangle), the diagonal from the pivots.
+// Returns a mask of the columns (bit 4 S + c) whose pivot is not positive
+// (zero, negative or NaN; the arithmetic goes on and its results are
+// discarded).
+__device__ __forceinline__ double mfma4_f64(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ double mfma4_f64_neg(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 2 /* neg B */);
 }
 
-// Block (bi, bj) of the resident tile -= P(bi) P(bj)^T, P the 16 columns of
-// the panel at c0.  A operand: P(bi) (rows on lanes % 16), B operand: P(bj)^T;
-// element v of lane l is then row 4v + l/16, column l%16 of the block.
-__device__ __forceinline__ void upd16_lds(double* As, int c0, int bi, int bj, int lane) {
-  const int l16 = lane & 15, lg = lane >> 4;
-  d4 acc;
+// Lanes 4 Q .. 4 Q + 3 of every row of 16 lanes, copied to the row's other quads.
+template <int Q>
+__device__ __forceinline__ double quad_to_row(double v) {
+  const long long b = __double_as_longlong(v);
+  int lo = (int)b, hi = (int)(b >> 32);
+  const int lo0 = lo, hi0 = hi;
+  lo = __builtin_amdgcn_update_dpp(lo, lo0, 0x120 + 4, 0xf, 1 << ((Q + 1) & 3), false);
+  hi = __builtin_amdgcn_update_dpp(hi, hi0, 0x120 + 4, 0xf, 1 << ((Q + 1) & 3), false);
+  lo = __builtin_amdgcn_update_dpp(lo, lo0, 0x120 + 8, 0xf, 1 << ((Q + 2) & 3), false);
+  hi = __builtin_amdgcn_update_dpp(hi, hi0, 0x120 + 8, 0xf, 1 << ((Q + 2) & 3), false);
+  lo = __builtin_amdgcn_update_dpp(lo, lo0, 0x120 + 12, 0xf, 1 << ((Q + 3) & 3), false);
+  hi = __builtin_amdgcn_update_dpp(hi, hi0, 0x120 + 12, 0xf, 1 << ((Q + 3) & 3), false);
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+struct Quad {
+  double fw;      // the solve operand
+  double d[4], y[4];  // the pivots and their reciprocal square roots
+};
+
+template <int S>
+__device__ __forceinline__ unsigned quad_factor(double xs, const double (&e)[4], int l16, Quad& q) {
+  double a[10], l[10];
+  {
+    int n = 0;
 #pragma unroll
-  for (int v = 0; v < 4; ++v) acc[v] = As[(bj * 16 + l16) * SLD + bi * 16 + 4 * v + lg];
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j <= i; ++j) a[n++] = readlane_f64(xs, 16 * j + 4 * S + i);
+  }
+  auto ix = [](int i, int j) __attribute__((always_inline)) { return i * (i + 1) / 2 + j; };
+  unsigned bad = 0;
+  double w[4];
+  q.fw = 0.0;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    double d = a[ix(c, c)];
+#pragma unroll
+    for (int t = 0; t < c; ++t) d = fma(-l[ix(c, t)], l[ix(c, t)], d);
+    bad |= ((unsigned)__builtin_amdgcn_ballot_w64(!(d > 0.0)) & 1u) << (4 * S + c);
+    const double y0 = __builtin_amdgcn_rsq(d);
+    const double er = fma(-(d * y0), y0, 1.0);
+    const double y = fma(y0 * er, fma(0.375, er, 0.5), y0);
+    q.d[c] = d;
+    q.y[c] = y;
+#pragma unroll
+    for (int i = c + 1; i < 4; ++i) {
+      double v = a[ix(i, c)];
+#pragma unroll
+      for (int t = 0; t < c; ++t) v = fma(-l[ix(i, t)], l[ix(c, t)], v);
+      l[ix(i, c)] = v * y;
+    }
+    // row c of this lane's column of the inverse
+    double t = e[c];
+#pragma unroll
+    for (int u = 0; u < c; ++u) t = fma(-l[ix(c, u)], w[u], t);
+    w[c] = t * y;
+    q.fw = ((l16 & 3) == c) ? w[c] : q.fw;
+  }
+  return bad;
+}
+
+// The operands of a panel's sub-steps in LDS, 64 doubles each: the four solve
+// operands, then those of the updates of quad i after sub-step s < i.
+#define QUAD_OPS 10
+__device__ __forceinline__ constexpr int quad_op(int s, int i) { return s == i ? s : 4 + (s == 0 ? i - 1 : s == 1 ? i + 1 : 5); }
+
+// One sub-step on the diagonal block xd (L's columns to lf) and one row
+// block x of the panel.  e[c] = (l / 16 == c).  Its operands also go to Fb.
+// Returns as quad_factor.
+template <int S>
+__device__ __forceinline__ unsigned panel_quad(d4& xd, d4& lf, d4& x, const double (&e)[4], int lane, double* Fb) {
+  const int l16 = lane & 15;
+  Quad q;
+  const unsigned bad = quad_factor<S>(xd[S], e, l16, q);
+  const double zd = mfma4_f64(q.fw, xd[S], 0.0);
+  double yq[4];  // yq[i]: the solved rows of quad i of the diagonal block
+  if constexpr (S < 3) {
+    yq[S + 1] = quad_to_row<S + 1>(zd);
+    xd[S + 1] = mfma4_f64_neg(yq[S + 1], zd, xd[S + 1]);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const double z = mfma4_f64(q.fw, x[S], 0.0);
+  if constexpr (S < 2) {
+    yq[S + 2] = quad_to_row<S + 2>(zd);
+    xd[S + 2] = mfma4_f64_neg(yq[S + 2], zd, xd[S + 2]);
+  }
+  if constexpr (S < 1) {
+    yq[S + 3] = quad_to_row<S + 3>(zd);
+    xd[S + 3] = mfma4_f64_neg(yq[S + 3], zd, xd[S + 3]);
+  }
+  xd[S] = zd;
+  double v = zd;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) v = (lane == 16 * c + 4 * S + c) ? q.d[c] * q.y[c] : v;
+  lf[S] = v;
+  x[S] = z;
+#pragma unroll
+  for (int i = S + 1; i < 4; ++i) {
+    x[i] = mfma4_f64_neg(yq[i], z, x[i]);
+    Fb[quad_op(S, i) * 64 + lane] = yq[i];
+  }
+  Fb[quad_op(S, S) * 64 + lane] = q.fw;
+  return bad;
+}
+
+// The 16 columns: panel_quad four times.  With x the identity on entry, x is
+// L_dd^{-T} on return.  Returns 0, or ibase + the 1-based column of the first
+// pivot that is not positive.
+__device__ __forceinline__ int panel16(d4& xd, d4& lf, d4& x, const double (&e)[4], int lane, int ibase,
+                                       double* Fb) {
+  unsigned bad = panel_quad<0>(xd, lf, x, e, lane, Fb);
+  bad |= panel_quad<1>(xd, lf, x, e, lane, Fb);
+  bad |= panel_quad<2>(xd, lf, x, e, lane, Fb);
+  bad |= panel_quad<3>(xd, lf, x, e, lane, Fb);
+  return bad ? ibase + __builtin_ctz(bad) + 1 : 0;
+}
+
+// Row blocks of the panel solved with the operands that panel16 left in Fb.
+template <int NX>
+__device__ __forceinline__ void panel16_rows(d4 (&x)[NX], const double* Fb, int lane) {
+  double f[QUAD_OPS];
+#pragma unroll
+  for (int k = 0; k < QUAD_OPS; ++k) f[k] = Fb[k * 64 + lane];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    const double fa = As[(c0 + 4 * s + lg) * SLD + bi * 16 + l16];
-    const double fb = As[(c0 + 4 * s + lg) * SLD + bj * 16 + l16];
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fa, fb, acc, 0, 0, 2 /* neg B */);
-  }
 #pragma unroll
-  for (int v = 0; v < 4; ++v) As[(bj * 16 + l16) * SLD + bi * 16 + 4 * v + lg] = acc[v];
+    for (int h = 0; h < NX; ++h) x[h][s] = mfma4_f64(f[quad_op(s, s)], x[h][s], 0.0);
+#pragma unroll
+    for (int i = s + 1; i < 4; ++i)
+#pragma unroll
+      for (int h = 0; h < NX; ++h) x[h][i] = mfma4_f64_neg(f[quad_op(s, i)], x[h][s], x[h][i]);
+  }
 }
 
-__device__ __forceinline__ int potrf_small(double* __restrict__ Akk, int64_t ld, int m, double* lds) {
-  double* As = lds;                      // [128][SLD]
-  double* Ldd = As + 128 * SLD;          // [PW][PW + 1]
-  double* Linv = Ldd + PW * (PW + 1);    // [PW]
+// ---------------------------------------------------------------------------
+// POTRF of a tile of order m <= 128 on one workgroup, the tile in LDS for the
+// whole factorization: right-looking by 16-column panels, every product on
+// the matrix cores.  FP64 vector and matrix instructions of a wavefront do
+// not overlap, so the chain of diagonal blocks has a wavefront of its own:
+//   wavefront 0     factors the diagonal block of panel j, with its inverse
+//                   (panel16), while
+//   wavefronts 1-3  apply panel j - 1 to the later columns;
+//   barrier         (the sub-steps' operands are in LDS)
+//   all             solve the panel's row blocks; wavefront 0 takes the block
+//                   below the diagonal and applies it to the next diagonal
+//                   block;
+//   barrier         (the panel is in LDS).
+//
+// With IV set, the tile's inverse comes along.  The rows of the identity, solved and
+// updated like rows below the tile, become L^{-T}; row block r of it enters
+// with panel r, where row block r of the tile itself has just become the
+// diagonal block.  Its blocks (r, c), c > r, thus take the place of the tile's
+// unused upper blocks, (r, r) that of the diagonal block.  L^{-1} goes to IV
+// (ldi), zeros above its diagonal included; rows and columns from m to the
+// next multiple of 16 are the identity's.
+//
+// Bound by the chain: per panel about 2900 cycles of panel16 (vector
+// instructions issue every 5 to 8 cycles for one wavefront) and 900 of the
+// two products, two barriers and their LDS round trips.
+// Returns 0, or the 1-based column (within the tile) whose pivot is not
+// positive (the columns before its panel's are then stored).
+#define SLD 144   // LDS leading dimension of the resident tile (fragment rows 128 bytes apart modulo 256: no conflicts)
+
+
+__device__ __forceinline__ int potrf_small(double* __restrict__ Akk, int64_t ld, int m, double* lds,
+                                           double* __restrict__ IV = nullptr, int64_t ldi = 0) {
+  static_assert(128 * SLD + (QUAD_OPS + 4) * 64 <= LDS_DOUBLES, "the tile must fit the workgroup LDS");
+  double* As = lds;             // [128][SLD]
+  double* Fb = As + 128 * SLD;      // [QUAD_OPS][64] the panel's operands
+  double* Lb = Fb + QUAD_OPS * 64;  // [4][64] L_dd as wavefront 0 holds it
   __shared__ int s_sinfo;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
   const int nblk = (m + 15) >> 4;
-  // the lower triangle into LDS, 16 loads in flight per thread; rows and
-  // columns past m hold the identity
+  const bool inv = IV != nullptr;
+  // element i of the 16 x 16 block (rb, cb) in the MFMA result layout, which
+  // is also the operand layout of its k-step i
+  auto at = [&](int rb, int cb, int i) __attribute__((always_inline)) -> double& {
+    return As[(cb * 16 + 4 * i + lg) * SLD + rb * 16 + l16];
+  };
+  // this lane's element of a block, in the tile and (transposed) in the inverse;
+  // a block's own offset is wave-uniform
+  double* const Al = Akk + (int64_t)lg * ld + l16;
+  double* const Il = inv ? IV + (int64_t)l16 * ldi + lg : nullptr;
+  // the lower blocks into LDS, a wavefront's (every fourth, by columns) all in flight at once
   {
-    constexpr int PER = 128 * 128 / NT, BATCH = 16;
-#pragma unroll 1
-    for (int u0 = 0; u0 < PER; u0 += BATCH) {
-      double v[BATCH];
-#pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        const int idx = tid + (u0 + u) * NT, c = idx >> 7, r = idx & 127;
-        v[u] = Akk[(int64_t)imin(c, m - 1) * ld + imin(imax(r, c), m - 1)];
+    double v[9][4];
+    int rb = wave, cb = 0;
+    auto settle = [&]() __attribute__((always_inline)) {
+      while (rb >= nblk && cb < nblk) {
+        ++cb;
+        rb = rb - nblk + cb;
       }
+    };
+    settle();
+    const int rb0 = rb, cb0 = cb;
 #pragma unroll
-      for (int u = 0; u < BATCH; ++u) {
-        const int idx = tid + (u0 + u) * NT, c = idx >> 7, r = idx & 127;
-        if (c < nblk * 16 && r < nblk * 16) As[c * SLD + r] = (r < m && c < m && r >= c) ? v[u] : (r == c ? 1.0 : 0.0);
+    for (int t = 0; t < 9; ++t) {
+      if (cb < nblk) {
+        if (rb * 16 + 16 <= m) {
+          const double* const p = Al + (int64_t)cb * 16 * ld + rb * 16;
+          // lanes above the diagonal read the diagonal's row instead
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[t][i] = p[(int64_t)(4 * i) * ld + (rb == cb ? imax(4 * i + lg - l16, 0) : 0)];
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int c = cb * 16 + 4 * i + lg, r = rb * 16 + l16;
+            v[t][i] = Akk[(int64_t)imin(c, m - 1) * ld + imin(imax(r, c), m - 1)];
+          }
+        }
+        rb += 4;
+        settle();
+      }
+    }
+    rb = rb0;
+    cb = cb0;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      if (cb < nblk) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int r = rb * 16 + l16, c = cb * 16 + 4 * i + lg;
+          at(rb, cb, i) = (r < m && c < m && r >= c) ? v[t][i] : (r == c ? 1.0 : 0.0);
+        }
+        rb += 4;
+        settle();
       }
     }
   }
-  __syncthreads();
+  lds_barrier();
+  // row block rb of the solved panel j: to LDS, and to the tile or the inverse
+  auto put = [&](int rb, int j, const d4& x) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) at(rb, j, i) = x[i];
+    if (rb > j) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (rb * 16 + l16 < m) st_dev(Al + (int64_t)(j * 16 + 4 * i) * ld + rb * 16, x[i]);
+    } else if (inv) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) st_dev(Il + (int64_t)(rb * 16) * ldi + j * 16 + 4 * i, x[i]);
+    }
+  };
+  // Panel j - 1 on column cb = j + q: blocks (rb, cb) of the tile (rb >= cb; the
+  // next diagonal block is wavefront 0's) and of the inverse (rb < j).  Three
+  // register sets take turns, so that a block's operands are requested before,
+  // and its result is written back after, the products of the block in between.
+  // Columns q = 0 .. 6 hold 7, 7, 6, 5, 4, 3, 2 blocks (inv): 0 and 6 go to
+  // wavefront 1, 1 and 5 to 2, 2 and 4 to 3, and 3 to wavefront 0 after its
+  // diagonal block.
+  auto trail = [&](int j, int q) __attribute__((always_inline)) {
+    struct Set {
+      int r;  // row block, past the last: none
+      double g[4];
+      d4 c;
+    };
+    const int cb = j + q;
+    if (cb >= nblk) return;
+    const int r1 = q == 0 ? cb + 1 : cb;  // first row block of the tile
+    int rb = inv ? 0 : r1;
+    double f[4];
+    Set sa, sb, sc;
+    const double* const Xp = &at(0, j - 1, 0);
+    double* const Cp = &at(0, cb, 0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f[k] = Xp[cb * 16 + 4 * k * SLD];
+    auto fetch = [&](Set& u) __attribute__((always_inline)) {
+      // (past the last block: that block again, unused, so that every turn
+      // issues the same reads and a wait for one set leaves the next in flight)
+      u.r = rb;
+      const int r = imin(rb, nblk - 1) * 16;
+      rb = inv && rb + 1 == j ? r1 : rb + 1;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) u.g[k] = Xp[r + 4 * k * SLD];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) u.c[i] = Cp[r + 4 * i * SLD];
+    };
+    auto multiply = [&](Set& u) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) u.c = __builtin_amdgcn_mfma_f64_16x16x4f64(f[k], u.g[k], u.c, 0, 0, 2 /* neg B */);
+    };
+    auto back = [&](Set& u) __attribute__((always_inline)) {
+      if (u.r >= nblk) return;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) Cp[u.r * 16 + 4 * i * SLD] = u.c[i];
+    };
+    fetch(sa);
+    sb.r = sc.r = nblk;
+    auto turn = [&](Set& cur, Set& nxt) __attribute__((always_inline)) {
+      back(nxt);
+      fetch(nxt);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(cur);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll 1
+    while (sa.r < nblk) {
+      turn(sa, sb);
+      if (sb.r >= nblk) break;
+      turn(sb, sc);
+      if (sc.r >= nblk) break;
+      turn(sc, sa);
+    }
+    back(sa);
+    back(sb);
+    back(sc);
+  };
   if (wave == 0) {
-    const int info = diag16_lds(As, 0, imin(16, m), Ldd, Linv, lane);
-    if (lane == 0) s_sinfo = info;
+    double e[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) e[c] = (lg == c) ? 1.0 : 0.0;
+    d4 xd;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) xd[i] = at(0, 0, i);
+#pragma unroll 1
+    for (int j = 0; j < nblk; ++j) {
+      d4 lf, x;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = (4 * i + lg == l16) ? 1.0 : 0.0;
+      const int info = __builtin_amdgcn_readfirstlane(panel16(xd, lf, x, e, lane, 16 * j, Fb));
+      if (lane == 0) s_sinfo = info;
+      if (j > 0) trail(j, 3);
+      lds_barrier();
+      if (info != 0) return info;
+      if (j + 1 < nblk) {
+        d4 xb[1];
+        d4& xr = xb[0];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xr[k] = at(j + 1, j, k);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xd[i] = at(j + 1, j + 1, i);
+        panel16_rows(xb, Fb, lane);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xd = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[k], xr[k], xd, 0, 0, 2 /* neg B */);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) at(j + 1, j, i) = xr[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        Lb[i * 64 + lane] = lf[i];
+        at(j, j, i) = x[i];
+      }
+      lds_barrier();
+    }
+    return 0;
   }
-  __syncthreads();
+  // the blocks of panel j that wavefront 0 left in LDS: L_dd and its inverse
+  // (wavefront 3), the block below (wavefront 2)
+  auto put_chain = [&](int j) __attribute__((always_inline)) {
+    if (wave == 3) {
+      d4 lf, x;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) lf[i] = Lb[i * 64 + lane];
+      if (inv) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = at(j, j, i);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = j * 16 + l16, c = j * 16 + 4 * i + lg;
+        if (r >= c && r < m) st_dev(Al + (int64_t)(j * 16 + 4 * i) * ld + j * 16, lf[i]);
+      }
+      if (inv) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) st_dev(Il + (int64_t)(j * 16) * ldi + j * 16 + 4 * i, x[i]);
+      }
+    } else if (wave == 2 && j + 1 < nblk) {
+      d4 x;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = at(j + 1, j, i);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if ((j + 1) * 16 + l16 < m) st_dev(Al + (int64_t)(j * 16 + 4 * i) * ld + (j + 1) * 16, x[i]);
+    }
+  };
+#pragma unroll 1
   for (int j = 0; j < nblk; ++j) {
-    const int c0 = j * 16;
+    if (j > 0) {
+      trail(j, wave - 1);
+      trail(j, 7 - wave);
+      put_chain(j - 1);
+    } else if (inv) {
+      // while the first diagonal block is factored: the zeros of the tile's
+      // upper blocks and of the inverse
+#pragma unroll 1
+      for (int zc = 1; zc < nblk; ++zc)
+#pragma unroll 1
+        for (int zr = wave - 1; zr < zc; zr += 3) {
+          double* const z = IV + ((int64_t)zc * 16 + lg) * ldi + zr * 16 + l16;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            at(zr, zc, i) = 0.0;
+            st_dev(z + (int64_t)(4 * i) * ldi, 0.0);
+          }
+        }
+    }
+    lds_barrier();
     const int info = __builtin_amdgcn_readfirstlane(s_sinfo);
     if (info != 0) return info;
-    // rows below the diagonal block: y := y L_dd^{-T}, one row per thread
-#pragma unroll 1
-    for (int r = c0 + 16 + tid; r < nblk * 16; r += NT) {
-      double y[PW];
+    // the panel's other row blocks: the tile's below j + 1, the inverse's above j
+    {
+      // at most three to a wavefront; absent ones are the last again, unused
+      auto block = [&](int p) __attribute__((always_inline)) { return inv ? (p < j ? p : p + 2) : j + 2 + p; };
+      d4 x[3];
 #pragma unroll
-      for (int c = 0; c < PW; ++c) y[c] = As[(c0 + c) * SLD + r];
+      for (int t = 0; t < 3; ++t) {
+        const int rb = imin(block(wave - 1 + 3 * t), nblk - 1);
 #pragma unroll
-      for (int c = 0; c < PW; ++c) {
-        y[c] *= Linv[c];
-#pragma unroll
-        for (int c2 = c + 1; c2 < PW; ++c2) y[c2] -= y[c] * Ldd[c2 * (PW + 1) + c];
+        for (int k = 0; k < 4; ++k) x[t][k] = at(rb, j, k);
       }
+      panel16_rows(x, Fb, lane);
 #pragma unroll
-      for (int c = 0; c < PW; ++c) As[(c0 + c) * SLD + r] = y[c];
-    }
-    __syncthreads();
-    if (j + 1 >= nblk) break;
-    // the panel's update of the trailing lower blocks; wavefront 0 first
-    // updates and factors the next diagonal block (the critical path)
-    const int nb2 = nblk - j - 1;
-    const int npair = nb2 * (nb2 + 1) / 2;
-    if (wave == 0) {
-      upd16_lds(As, c0, j + 1, j + 1, lane);
-      const int info2 = diag16_lds(As, c0 + 16, imin(16, m - c0 - 16), Ldd, Linv, lane);
-      if (lane == 0) s_sinfo = info2;
-    }
-    // block pairs p >= 1 in column-major order of (bi >= bj), after (j+1, j+1),
-    // on the other three wavefronts (wavefront 0 is busy with the diagonal)
-#pragma unroll 1
-    for (int p = (wave == 0 ? npair : wave); p < npair; p += 3) {
-      int cj = 0, rem = p;
-      while (rem >= nb2 - cj) {
-        rem -= nb2 - cj;
-        ++cj;
+      for (int t = 0; t < 3; ++t) {
+        const int rb = block(wave - 1 + 3 * t);
+        if (rb < nblk) put(rb, j, x[t]);
       }
-      const int bj = j + 1 + cj;
-      upd16_lds(As, c0, bj + rem, bj, lane);
     }
-    __syncthreads();
+    lds_barrier();
   }
-  // the factor to the tile, lower triangle only
-  for (int idx = tid; idx < m * 128; idx += NT) {
-    const int c = idx >> 7, r = idx & 127;
-    if (r < m && r >= c) st_dev(Akk + (int64_t)c * ld + r, As[c * SLD + r]);
-  }
+  put_chain(nblk - 1);
   return 0;
 }
 
@@ -1409,7 +1755,7 @@ __device__ __forceinline__ void trsm_strip(TX* __restrict__ X, int64_t ldx, cons
       }
     }
   }
-  if constexpr (REV == 2) {
+  if (REV == 2 && Qb != nullptr) {
     for (int idx = tid; idx < S * mk; idx += NT) {
       const int rr = idx / mk, c = idx - rr * mk;
       st_dev(Qb + (int64_t)rr * ldq + c, Xs[(rr >> 4) * 8192 + c * 16 + (rr & 15)]);
@@ -1438,6 +1784,143 @@ __device__ __forceinline__ void trsm_inv_rows(double* __restrict__ X, int64_t ld
       gemm_core<SEG, GB, GB, 16, 2, 4>(X + (int64_t)c0 * ld, X, Linv + c0, ld, M, N, K, false, lds, nullptr, 0, -1,
                                        true, nb, true);
   }
+}
+
+// The same for a tile of order mk <= 128 (a multiple of 16): S <= 32 rows of
+// A_ik, X := X L_kk^{-T}, small enough to hold every operand in registers.
+// Wavefront w takes the 16-column blocks w and 7 - w of the result (together
+// the same work for every wavefront: block c needs the 16 (c + 1) columns up
+// to its own), requests all its fragments of L_kk^{-1} and X at once and
+// stores after every wavefront has its part of X.  Bound by that one memory
+// round trip and 72 products per wavefront.
+__device__ __forceinline__ void trsm_inv_strip(double* __restrict__ X, int64_t ld, const double* __restrict__ Linv,
+                                               int64_t nb, int S, int mk) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
+  const int nblk = mk >> 4;
+  const double* const Xl = X + (int64_t)lg * ld + imin(l16, S - 1);
+  const int64_t r1 = imin(16 + l16, S - 1) - imin(l16, S - 1);
+  const double* const Ll = Linv + (int64_t)lg * nb + l16;
+  const int ca = wave, cz = 7 - wave;  // ca < cz
+  double fa[16], fz[32], x[2][32];
+  // k-steps 4 t .. 4 t + 3 are block column t of L_kk^{-1}
+#pragma unroll
+  for (int t = 0; t < 8; ++t)
+    if (t < nblk && t <= (cz < nblk ? cz : ca)) {
+#pragma unroll
+      for (int k = 4 * t; k < 4 * t + 4; ++k) {
+        x[0][k] = Xl[(int64_t)(4 * k) * ld];
+        x[1][k] = Xl[(int64_t)(4 * k) * ld + r1];
+        if (cz < nblk) fz[k] = Ll[(int64_t)(4 * k) * nb + cz * 16];
+        if (t < 4 && t <= ca && ca < nblk) fa[k < 16 ? k : 0] = Ll[(int64_t)(4 * k) * nb + ca * 16];
+      }
+    }
+  d4 acc[2][2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int g = 0; g < 2; ++g) acc[b][g] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    if (cz < nblk && t <= cz) {
+#pragma unroll
+      for (int k = 4 * t; k < 4 * t + 4; ++k) {
+        acc[1][0] = mfma_f64(fz[k], x[0][k], acc[1][0]);
+        acc[1][1] = mfma_f64(fz[k], x[1][k], acc[1][1]);
+      }
+    }
+    if (t < 4 && ca < nblk && t <= ca) {
+#pragma unroll
+      for (int k = 4 * t; k < 4 * t + 4; ++k) {
+        acc[0][0] = mfma_f64(fa[k < 16 ? k : 0], x[0][k], acc[0][0]);
+        acc[0][1] = mfma_f64(fa[k < 16 ? k : 0], x[1][k], acc[0][1]);
+      }
+    }
+  }
+  // every wavefront's products must be done, so that its part of X has been read
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int g = 0; g < 2; ++g) asm volatile("" : : "v"(acc[b][g]));
+  lds_barrier();
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int cb = b == 0 ? ca : cz;
+    if (cb < nblk) {
+      double* const Xs = X + ((int64_t)cb * 16 + lg) * ld + l16;
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+        if (16 * g + l16 < S) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) st_dev(Xs + (int64_t)(4 * i) * ld + 16 * g, acc[b][g][i]);
+        }
+    }
+  }
+}
+
+// C[M x N] -= Ap[M x K] Bp[N x K]^T for M, N <= 64, K <= 128 a multiple of 16:
+// an update on the critical path of a factorization by small tiles.  Every
+// fragment goes straight from memory to registers, all requested at once (a
+// K this short does not repay stages in LDS); 2 x 2 wavefronts of 32 x 32.
+// The products come in the order of gemm_core's.
+__device__ __forceinline__ void gemm_reg64(double* __restrict__ C, const double* __restrict__ Ap,
+                                           const double* __restrict__ Bp, int64_t ld, int M, int N, int K,
+                                           bool lower_only) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
+  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
+  if (wr >= M || wc >= N || (lower_only && wc > wr)) return;
+  const double* A0[2];
+  const double* B0[2];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    A0[g] = Ap + (int64_t)lg * ld + imin(wr + 16 * g + l16, M - 1);
+    B0[g] = Bp + (int64_t)lg * ld + imin(wc + 16 * g + l16, N - 1);
+  }
+  double fa[2][32], fb[2][32];
+  d4 acc[2][2];
+#pragma unroll
+  for (int t = 0; t < 8; ++t)
+    if (16 * t < K) {
+#pragma unroll
+      for (int k = 4 * t; k < 4 * t + 4; ++k)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          fa[g][k] = A0[g][(int64_t)(4 * k) * ld];
+          fb[g][k] = B0[g][(int64_t)(4 * k) * ld];
+        }
+    }
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = wr + 16 * r + l16, col = wc + 16 * c + 4 * i + lg;
+        acc[r][c][i] = C[(int64_t)imin(col, N - 1) * ld + imin(row, M - 1)];
+      }
+#pragma unroll
+  for (int t = 0; t < 8; ++t)
+    if (16 * t < K) {
+#pragma unroll
+      for (int k = 4 * t; k < 4 * t + 4; ++k)
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+            acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[c][k], fa[r][k], acc[r][c], 0, 0, 2 /* neg B */);
+    }
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = wr + 16 * r + l16, col = wc + 16 * c + 4 * i + lg;
+        if (row < M && col < N && (!lower_only || row >= col)) st_dev(C + (int64_t)col * ld + row, acc[r][c][i]);
+      }
 }
 
 // ---------------------------------------------------------------------------
@@ -2635,7 +3118,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
     };
     // in a batched launch a system whose factorization failed only passes
     // its remaining tasks on, so that the DAG drains
-    const bool skip = a.batched && uniform_i(ld_relaxed(&a.sinfo[sid])) != 0;
+    const bool skip = a.batched && uniform_i(ld_relaxed(&a.sinfo[a.batched == 2 ? 0 : sid])) != 0;
     int ok = 1;
     // A unit of a POTRF pool runs the POTRF, TRSM or GEMM body on sub-blocks
     // of the diagonal tile (tk, tk): po_* give the sub-block offsets (rows,
@@ -2709,8 +3192,9 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
           const bool sub = unit >= 0;
           const int m = sub ? po_m : tsz(tk);
           E* Akk = Abase + (tk * nb + po_k) * ld + tk * nb + po_k;
+          // a whole tile's inverse comes along when the launch's TRSMs apply it
           if (m <= PSB)
-            info = uniform_i(potrf_small(Akk, ld, m, lds));
+            info = uniform_i(potrf_small(Akk, ld, m, lds, a.finv != 0 && !sub ? DinvSys + (int64_t)tk * nb * nb : nullptr, nb));
           else
             info = uniform_i(potrf_tile<SEG>(Akk, ld, m, lds));
           if (info != 0) info += po_k;
@@ -2748,10 +3232,15 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
               trsm_strip(Abase + (tk * nb) * ld + ti * nb + r0, ld, Dk, nb, S, tsz(tk), lds);
           }
         } else if (a.inv != 0 && unit < 0) {
-          // a 128-row block of A_ik through L_kk^{-1} (the launch's TRTRI(k))
-          const int r0 = part * GB;
-          trsm_inv_rows<SEG>(Abase + (tk * nb) * ld + ti * nb + r0, ld, DinvSys + (int64_t)tk * nb * nb, nb,
-                             imin(GB, tsz(ti) - r0), tsz(tk), lds);
+          // a block of inv_rows rows of A_ik through L_kk^{-1} (from POTRF(k) with
+          // finv, else from the launch's TRTRI(k))
+          const int r0 = part * a.inv_rows, M = imin(a.inv_rows, tsz(ti) - r0);
+          E* const Xr = Abase + (tk * nb) * ld + ti * nb + r0;
+          const double* const Li = DinvSys + (int64_t)tk * nb * nb;
+          if (tsz(tk) <= PSB)
+            for (int r = 0; r < M; r += TS) trsm_inv_strip(Xr + r, ld, Li, nb, imin(TS, M - r), tsz(tk));
+          else
+            trsm_inv_rows<SEG>(Xr, ld, Li, nb, M, tsz(tk), lds);
         } else {
           // a strip of A_ik, or of sub-block (r, b) of the diagonal tile for a pool unit
           const bool sub = unit >= 0;
@@ -2779,11 +3268,11 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
           sj = part - si * (si + 1) / 2;
           bm = bn = a.syrk_b;
         } else {
-          const int ncj = (tsz(tj) + a.gemm_n - 1) / a.gemm_n;
+          bm = kind == TK_GEMM ? a.gemm1_m : a.gemm_m;
+          bn = kind == TK_GEMM ? a.gemm1_n : a.gemm_n;
+          const int ncj = (tsz(tj) + bn - 1) / bn;
           si = part / ncj;
           sj = part % ncj;
-          bm = a.gemm_m;
-          bn = a.gemm_n;
         }
         int M = imin(bm, tsz(ti) - si * bm);
         int N = imin(bn, tsz(tj) - sj * bn);
@@ -2839,7 +3328,10 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
             ok = 0;
             break;
           }
-          gemm_nt<SEG>(C, Ap, Bp, ld, M, N, K, lower, lds);
+          if (bm == 64 && K <= PSB)
+            gemm_reg64(C, Ap, Bp, ld, M, N, K, lower);
+          else
+            gemm_nt<SEG>(C, Ap, Bp, ld, M, N, K, lower, lds);
         }
         break;
       }
@@ -2922,9 +3414,9 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
           }
           wait_vmcnt<0>();
           __syncthreads();
-          if constexpr (MODE == 0)  // with L_kk^{-1} too (Dinv), which the TRSM items apply
+          if constexpr (MODE == 0)  // with L_kk^{-1} too (Dinv), if the TRSM items apply it (and not POTRF(k)'s)
             trsm_strip<double, 2>(X, nb, Abase + (tk * nb) * ld + tk * nb, ld, S, mpad, lds,
-                                  DinvSys + (int64_t)tk * nb * nb + (int64_t)r0 * nb, nb);
+                                  a.finv ? nullptr : DinvSys + (int64_t)tk * nb * nb + (int64_t)r0 * nb, nb);
           else if constexpr (MODE == 3)  // the adjoint: L (its A) is the factor
             trsm_strip<double>(X, nb, Abase + (tk * nb) * ld + tk * nb, ld, S, mpad, lds);
           else
