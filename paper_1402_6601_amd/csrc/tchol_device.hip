@@ -66,10 +66,10 @@ __device__ __forceinline__ double readlane_f64(double v, int l) {
 // barrier) before reading the stage they fill.  M0 is set in the same
 // statement, right before the load; it is a reserved register the compiler
 // sets itself before each of its own uses (these kernels have none).
-typedef __attribute__((address_space(3))) void lds_void_t;
-
+// (the low word of a generic pointer into LDS is the LDS byte address; a cast
+// of the pointer to LDS would add a test for null to every transfer)
 __device__ __forceinline__ uint32_t lds_addr(double* l) {
-  return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_t*)l);
+  return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)l);
 }
 __device__ __forceinline__ void dma16(const void* g, double* l) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr(l)), "v"(g) : "memory");
@@ -91,6 +91,19 @@ __device__ __forceinline__ void dma16s(const void* base, uint32_t off, double* l
 __device__ __forceinline__ void dma4s(const void* base, uint32_t off, double* l) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds_addr(l)), "v"(off), "s"(uniform_ptr(base))
                : "memory");
+}
+
+// The same with the LDS address as a wave-uniform byte address plus a
+// constant, one scalar add in all.
+template <int IMM>
+__device__ __forceinline__ void dma16i(uint64_t base, uint32_t off, uint32_t l) {
+  asm volatile("s_add_u32 m0, %0, %1\n\tglobal_load_lds_dwordx4 %2, %3" : : "s"(l), "n"(IMM), "v"(off), "s"(base)
+               : "memory", "scc");
+}
+template <int IMM>
+__device__ __forceinline__ void dma4i(uint64_t base, uint32_t off, uint32_t l) {
+  asm volatile("s_add_u32 m0, %0, %1\n\tglobal_load_lds_dword %2, %3" : : "s"(l), "n"(IMM), "v"(off), "s"(base)
+               : "memory", "scc");
 }
 
 constexpr int imin_c(int a, int b) { return a < b ? a : b; }
@@ -145,6 +158,15 @@ __device__ __forceinline__ void split3(double x, uint32_t& h, uint32_t& m, uint3
   const double r1 = x - bf16_val(h);
   m = bf16_rne((float)r1);
   l = bf16_rne((float)(r1 - bf16_val(m)));
+}
+
+// f(0), ..., f(N - 1) with compile-time arguments.
+template <int N, class F, int I = 0>
+__device__ __forceinline__ void static_for(F f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>());
+    static_for<N, F, I + 1>(f);
+  }
 }
 
 // s_waitcnt vmcnt(N) with the other counters left alone (gfx9 encoding).
@@ -390,27 +412,230 @@ __device__ __forceinline__ void gemm_core(double* __restrict__ C, const double* 
       }
 }
 
-// GEMM / SYRK work item: a 128 x 128 sub-tile of C, K = nb.  Chunks of 32
-// columns through two stages need half the workgroup barriers of chunks of
-// 16 through four; a K that is only a multiple of 16 takes the latter.
+// GEMM / SYRK work item: a 128 x 128 sub-tile of C -= Ap Bp^T (or, zero_c with
+// neg, C := Ap Bp^T), M, N <= 128, K a multiple of 16.  2 x 2 wavefronts of
+// 64 x 64; the panels stream through four LDS stages of 16 columns, as in
+// gemm_kloop (SEG, row clamping and alignment as there).  What differs, to
+// keep the matrix cores fed between chunks and at the ends of the item:
+//  - a chunk has landed one whole chunk before its products start, so the
+//    first fragments of the next chunk are read under the current one's last
+//    products, and the barrier between them finds the next products ready;
+//  - a transfer costs four scalar-side instructions (a running pointer per
+//    panel, the LDS address from one base), and what a k-step issues besides
+//    its products is spread between them in small groups: a wavefront issues
+//    in order, and whatever takes longer than the product before it leaves
+//    the matrix core idle;
+//  - the product is accumulated from zero and C is subtracted at the end: C is
+//    requested once the last transfer has landed, two chunks before the end,
+//    and its memory time passes under their products.
+// Per 128 x 128 item, all 256 workgroups busy, K = 1024 (n = 16384) 138 -> 127
+// us and K = 256 (tiles of 128, n = 8192) 43 -> 39 us, of which the products
+// take 109 and 27 us at 2.4 GHz: 1.9 us per 16-column chunk against 1.7, 2.8
+// us before the first product, 1.4 us of C not hidden, 2.4 us of stores.
 #define GB 128
+template <int SEG>
+__device__ __forceinline__ void gemm_tile(double* __restrict__ C, int64_t ldC, const double* __restrict__ Ap, int64_t ld,
+                                          const double* __restrict__ Bp, int64_t ldB, int M, int N, int K,
+                                          bool lower_only, bool zero_c, bool neg, double* lds) {
+  constexpr int KC = 16, NST = 4, XLD = GB + 2, STAGE = 2 * KC * XLD;
+  constexpr int Q = KC * GB / SEG;     // transfers per panel and stage
+  constexpr int J = 2 * Q / 4;         // per wavefront: J / 2 of A, then J / 2 of B
+  constexpr int PER = J / (KC / 4);    // per k-step
+  constexpr int ROWS = 4 * SEG / GB;   // k-rows that a round of the four wavefronts covers
+  static_assert(NST * STAGE <= LDS_DOUBLES && J * 4 == 2 * Q && PER * (KC / 4) == J && J <= 63 && ROWS >= 1,
+                "stages and transfers");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int l16 = lane & 15, lg = lane >> 4;
+
+  // this wavefront's transfers: segment wave + 4 j of a panel, j counting on
+  // from chunk to chunk, so a running pointer per panel; rows clamped to the
+  // last valid start row as in gemm_kloop
+  const int le = SEG == 128 ? 2 * lane : (lane >> 1);
+  const int u = (wave * SEG) % GB, cu = (wave * SEG) / GB;
+  auto lane_off = [&](int V) __attribute__((always_inline)) {
+    return (uint32_t)(imin(u + le, SEG == 128 ? ((V - 1) & ~1) : V - 1) * 8 + (SEG == 128 ? 0 : 4 * (lane & 1)));
+  };
+  const uint32_t offa = lane_off(M), offb = lane_off(N);
+  uint64_t pa = (uint64_t)(uintptr_t)uniform_ptr(Ap + (int64_t)cu * ld);
+  uint64_t pb = (uint64_t)(uintptr_t)uniform_ptr(Bp + (int64_t)cu * ldB);
+  const uint64_t da = (uint64_t)(ROWS * 8) * (uint64_t)ld, db = (uint64_t)(ROWS * 8) * (uint64_t)ldB;
+  const uint32_t l0 = lds_addr(lds) + (uint32_t)(cu * XLD + u) * 8;
+  auto slot = [&](auto jc, uint32_t st) __attribute__((always_inline)) {
+    constexpr int j = decltype(jc)::value;
+    constexpr int imm = (j < J / 2 ? j * ROWS : KC + (j - J / 2) * ROWS) * XLD * 8;
+    if constexpr (j < J / 2) {
+      if constexpr (SEG == 128) dma16i<imm>(pa, offa, st);
+      else dma4i<imm>(pa, offa, st);
+      pa += da;
+    } else {
+      if constexpr (SEG == 128) dma16i<imm>(pb, offb, st);
+      else dma4i<imm>(pb, offb, st);
+      pb += db;
+    }
+  };
+  auto issue = [&](int ch) __attribute__((always_inline)) {
+    const uint32_t st = l0 + (uint32_t)(ch % NST) * (STAGE * 8);
+    static_for<J>([&](auto jc) __attribute__((always_inline)) { slot(jc, st); });
+  };
+  d4 acc[4][4];
+#pragma unroll
+  for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = d4{0.0, 0.0, 0.0, 0.0};
+  double fa[2][4], fb[2][4];
+  const double* const fa0 = lds + lg * XLD + wm * 64 + l16;
+  const double* const fb0 = lds + (KC + lg) * XLD + wn * 64 + l16;
+  auto read_a = [&](int so, int ks, int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb) fa[buf][rb] = fa0[so + ks * 4 * XLD + rb * 16];
+  };
+  auto read_b = [&](int so, int ks, int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) fb[buf][cb] = fb0[so + ks * 4 * XLD + cb * 16];
+  };
+  // the products of the chunk in the stage at so (doubles), the first fragments
+  // of the next one, at sn; with ISSUE the transfers of the chunk for stage
+  // st go out along them, else extra(k-step, group of products) is called
+  auto compute = [&](auto issue_c, int so, int sn, uint32_t st, auto extra) __attribute__((always_inline)) {
+    constexpr bool ISSUE = decltype(issue_c)::value;
+    static_for<KC / 4>([&](auto kc) __attribute__((always_inline)) {
+      constexpr int ks = decltype(kc)::value, cur = ks & 1, nxt = cur ^ 1;
+      constexpr bool last = ks + 1 == KC / 4;
+      auto products = [&](int rb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) acc[rb][cb] = mfma_f64(fb[cur][cb], fa[cur][rb], acc[rb][cb]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!ISSUE) extra(kc, rb);
+      };
+      products(0);
+      // (after the last chunk: a stage that is not read, so no condition)
+      read_a(last ? sn : so, last ? 0 : ks + 1, nxt);
+      __builtin_amdgcn_sched_barrier(0);
+      products(1);
+      read_b(last ? sn : so, last ? 0 : ks + 1, nxt);
+      __builtin_amdgcn_sched_barrier(0);
+      products(2);
+      if constexpr (ISSUE)
+        static_for<PER / 2>([&](auto jj) __attribute__((always_inline)) {
+          slot(std::integral_constant<int, ks * PER + decltype(jj)::value>(), st);
+        });
+      __builtin_amdgcn_sched_barrier(0);
+      products(3);
+      if constexpr (ISSUE)
+        static_for<PER - PER / 2>([&](auto jj) __attribute__((always_inline)) {
+          slot(std::integral_constant<int, ks * PER + PER / 2 + decltype(jj)::value>(), st);
+        });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  const int nch = K / KC;
+#pragma unroll
+  for (int p = 0; p < NST - 1; ++p)
+    if (p < nch) issue(p);
+  // chunks 0 and 1 landed (everything, when there is no third)
+  if (nch >= 3) wait_vmcnt<J>();
+  else wait_vmcnt<0>();
+  lds_barrier();
+  read_a(0, 0, 0);
+  read_b(0, 0, 0);
+  auto nothing = [](auto, int) __attribute__((always_inline)) {};
+  int so = 0;  // the current chunk's stage
+  auto after = [&](int o) __attribute__((always_inline)) { return o == (NST - 1) * STAGE ? 0 : o + STAGE; };
+  int ch = 0;
+  for (; ch + NST - 1 < nch; ++ch) {
+    const int sn = after(so), sw = so == 0 ? (NST - 1) * STAGE : so - STAGE;
+    compute(std::true_type(), so, sn, l0 + (uint32_t)sw * 8, nothing);
+    so = sn;
+    wait_vmcnt<J>();  // chunk ch + 2 has landed, ch + 3 may be in flight
+    lds_barrier();
+  }
+  for (; ch + 2 < nch; ++ch) {  // at most one: nothing left to issue
+    const int sn = after(so);
+    compute(std::false_type(), so, sn, 0, nothing);
+    so = sn;
+    wait_vmcnt<0>();
+    lds_barrier();
+  }
+  // the last two chunks, with C on the way: of a whole tile four loads after
+  // every group of the first one's products (all at once they would fill the
+  // memory pipeline and hold up the products), at one pointer per column of a lane and
+  // constant row offsets (address arithmetic in vector instructions would
+  // cost more than the loads)
+  const bool whole = M == GB && N == GB;
+  double* const Cl = C + (int64_t)(wn * 64 + lg) * ldC + wm * 64 + l16;
+  const bool early = whole && !zero_c && nch >= 2;
+  double c[4][4][4];
+  if (zero_c) {
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[rb][cb][i] = 0.0;
+  } else if (!early) {
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = wm * 64 + rb * 16 + l16, col = wn * 64 + cb * 16 + 4 * i + lg;
+          c[rb][cb][i] = C[(int64_t)imin(col, N - 1) * ldC + imin(row, M - 1)];
+        }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if (nch >= 2) {  // (both chunks landed before: no wait, no barrier between them)
+    const int sn = after(so);
+    compute(std::false_type(), so, sn, 0, [&](auto kc, int g) __attribute__((always_inline)) {
+      constexpr int ks = decltype(kc)::value;  // column block ks, element g of its columns
+      if (early) {
+        const double* const q = Cl + (int64_t)(ks * 16 + 4 * g) * ldC;
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) c[rb][ks][g] = q[rb * 16];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
+    so = sn;
+  }
+  compute(std::false_type(), so, after(so), 0, nothing);
+  lds_barrier();  // every wavefront is done with the stages before LDS is reused
+  const double sgn = neg ? -1.0 : 1.0;
+  if (whole && !lower_only) {
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        double* const q = Cl + (int64_t)(cb * 16 + 4 * i) * ldC;
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) st_dev(q + rb * 16, sgn * (c[rb][cb][i] - acc[rb][cb][i]));
+      }
+  } else {
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = wm * 64 + rb * 16 + l16, col = wn * 64 + cb * 16 + 4 * i + lg;
+          if (row < M && col < N && (!lower_only || row >= col))
+            st_dev(C + (int64_t)col * ldC + row, sgn * (c[rb][cb][i] - acc[rb][cb][i]));
+        }
+  }
+}
+
 template <int SEG>
 __device__ __forceinline__ void gemm_nt(double* C, const double* Ap, const double* Bp, int64_t ld, int M, int N,
                                         int K, bool lower_only, double* lds) {
-  if (K % 32 == 0)
-    gemm_core<SEG, GB, GB, 32, 2, 2>(C, Ap, Bp, ld, M, N, K, lower_only, lds);
-  else
-    gemm_core<SEG, GB, GB, 16, 2, 4>(C, Ap, Bp, ld, M, N, K, lower_only, lds);
+  gemm_tile<SEG>(C, ld, Ap, ld, Bp, ld, M, N, K, lower_only, false, false, lds);
 }
 
 // The same product with C at its own leading dimension ldc (the panels at
 // ld), optionally starting from C = 0.
 __device__ __forceinline__ void gemm_nt_ex(double* C, int64_t ldc, const double* Ap, const double* Bp, int64_t ld,
                                            int M, int N, int K, bool lower_only, bool zero_c, double* lds) {
-  if (K % 32 == 0)
-    gemm_core<128, GB, GB, 32, 2, 2>(C, Ap, Bp, ld, M, N, K, lower_only, lds, nullptr, 0, ldc, zero_c);
-  else
-    gemm_core<128, GB, GB, 16, 2, 4>(C, Ap, Bp, ld, M, N, K, lower_only, lds, nullptr, 0, ldc, zero_c);
+  gemm_tile<128>(C, ldc, Ap, ld, Bp, ld, M, N, K, lower_only, zero_c, false, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1776,13 +2001,7 @@ __device__ __forceinline__ void trsm_inv_rows(double* __restrict__ X, int64_t ld
                                               int64_t nb, int M, int mk, double* lds) {
   for (int c0 = ((mk - 1) / GB) * GB; c0 >= 0; c0 -= GB) {
     const int N = imin(GB, mk - c0), K = c0 + N;
-    // C = 0 - X Linv^T over K, stored negated
-    if (K % 32 == 0)
-      gemm_core<SEG, GB, GB, 32, 2, 2>(X + (int64_t)c0 * ld, X, Linv + c0, ld, M, N, K, false, lds, nullptr, 0, -1,
-                                       true, nb, true);
-    else
-      gemm_core<SEG, GB, GB, 16, 2, 4>(X + (int64_t)c0 * ld, X, Linv + c0, ld, M, N, K, false, lds, nullptr, 0, -1,
-                                       true, nb, true);
+    gemm_tile<SEG>(X + (int64_t)c0 * ld, ld, X, ld, Linv + c0, nb, M, N, K, false, true, true, lds);
   }
 }
 
@@ -1863,7 +2082,7 @@ __device__ __forceinline__ void trsm_inv_strip(double* __restrict__ X, int64_t l
 // an update on the critical path of a factorization by small tiles.  Every
 // fragment goes straight from memory to registers, all requested at once (a
 // K this short does not repay stages in LDS); 2 x 2 wavefronts of 32 x 32.
-// The products come in the order of gemm_core's.
+// The products come in the order of gemm_tile's.
 __device__ __forceinline__ void gemm_reg64(double* __restrict__ C, const double* __restrict__ Ap,
                                            const double* __restrict__ Bp, int64_t ld, int M, int N, int K,
                                            bool lower_only) {
@@ -1880,7 +2099,7 @@ __device__ __forceinline__ void gemm_reg64(double* __restrict__ C, const double*
     B0[g] = Bp + (int64_t)lg * ld + imin(wc + 16 * g + l16, N - 1);
   }
   double fa[2][32], fb[2][32];
-  d4 acc[2][2];
+  d4 acc[2][2], c0[2][2];
 #pragma unroll
   for (int t = 0; t < 8; ++t)
     if (16 * t < K) {
@@ -1899,7 +2118,8 @@ __device__ __forceinline__ void gemm_reg64(double* __restrict__ C, const double*
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = wr + 16 * r + l16, col = wc + 16 * c + 4 * i + lg;
-        acc[r][c][i] = C[(int64_t)imin(col, N - 1) * ld + imin(row, M - 1)];
+        c0[r][c][i] = C[(int64_t)imin(col, N - 1) * ld + imin(row, M - 1)];
+        acc[r][c][i] = 0.0;
       }
 #pragma unroll
   for (int t = 0; t < 8; ++t)
@@ -1910,7 +2130,7 @@ __device__ __forceinline__ void gemm_reg64(double* __restrict__ C, const double*
         for (int r = 0; r < 2; ++r)
 #pragma unroll
           for (int c = 0; c < 2; ++c)
-            acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[c][k], fa[r][k], acc[r][c], 0, 0, 2 /* neg B */);
+            acc[r][c] = mfma_f64(fb[c][k], fa[r][k], acc[r][c]);
     }
 #pragma unroll
   for (int r = 0; r < 2; ++r)
@@ -1919,7 +2139,7 @@ __device__ __forceinline__ void gemm_reg64(double* __restrict__ C, const double*
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = wr + 16 * r + l16, col = wc + 16 * c + 4 * i + lg;
-        if (row < M && col < N && (!lower_only || row >= col)) st_dev(C + (int64_t)col * ld + row, acc[r][c][i]);
+        if (row < M && col < N && (!lower_only || row >= col)) st_dev(C + (int64_t)col * ld + row, c0[r][c][i] - acc[r][c][i]);
       }
 }
 
@@ -2821,14 +3041,20 @@ __device__ __forceinline__ int uniform_i(int v) { return __builtin_amdgcn_readfi
 // must never end up inside lane-masked loop structure.  Waits until the
 // task's counter reaches zero; false when the run is being aborted or the
 // wait exceeded its bound.
-__device__ __forceinline__ bool wait_ready(const KArgs& a, int task, int lane) {
-  const int dep0 = ld_relaxed(&a.dep[task]), abort0 = ld_relaxed(&a.hdr[HDR_ABORT]);  // both in flight at once
+// one (not null): a single-matrix launch's failure word, read along with the
+// first look (and again after a wait) into failed.
+__device__ __forceinline__ bool wait_ready(const KArgs& a, int task, int lane, const int32_t* one, int& failed) {
+  const int dep0 = ld_relaxed(&a.dep[task]), abort0 = ld_relaxed(&a.hdr[HDR_ABORT]);  // all in flight at once
+  const int f0 = one ? ld_relaxed(one) : 0;
+  failed = uniform_i(f0);
   if (uniform_i(dep0) == 0) return uniform_i(abort0) == 0;
   const uint64_t t0 = wall_clock64();
   for (;;) {
     __builtin_amdgcn_s_sleep(2);
     // the counter and the abort flag in flight together: one round trip per poll
-    const int d = ld_relaxed(&a.dep[task]), ab = uniform_i(ld_relaxed(&a.hdr[HDR_ABORT]));
+    const int d = ld_relaxed(&a.dep[task]), f = one ? ld_relaxed(one) : 0;
+    const int ab = uniform_i(ld_relaxed(&a.hdr[HDR_ABORT]));
+    failed = uniform_i(f);
     if (uniform_i(d) == 0) return ab == 0;
     if (ab != 0) return false;
     if ((int64_t)(wall_clock64() - t0) > a.wait_limit) {
@@ -2979,7 +3205,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
   static_assert(FRB_COMPACT_DOUBLES <= PT_LDS_COMPACT, "compact LDS budget");
   constexpr bool COMPACT = MODE == 6 || MODE == 7;
   __shared__ double lds[COMPACT ? PT_LDS_COMPACT : LDS_DOUBLES];
-  __shared__ int s_claim[4];
+  __shared__ int s_claim[5];
   __shared__ int32_t s_desc[DESC_WORDS];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = uniform_i(tid >> 6);
@@ -2991,13 +3217,20 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
   // the POTRF work item's record, published when the pool has run dry
   int pl_task = -1, pl_m = 0, pl_ticket = 0, pl_parts = 0, pl_e0 = 0, pl_e1 = 0;
   int32_t* pl_pool = nullptr;
+  // a launch of one matrix (nsys <= 2: its factor's and its solve's tile size)
+  // keeps the system records in LDS and has one failure word, which the claim
+  // reads along with the task's counter: fewer round trips before an item starts
+  __shared__ int64_t s_sys[2 * SYS_WORDS];
+  const bool one_matrix = !COMPACT && a.nsys <= 2 && (a.nsys == 1 || a.batched == 2);
+  if (one_matrix && tid < a.nsys * SYS_WORDS) s_sys[tid] = a.sys[tid];
+  const int32_t* const one_failed = one_matrix && a.batched ? a.sinfo : nullptr;
   for (;;) {
     // publish + claim: wavefront 0 marks the previous item done and takes the
     // next ticket in the same round trip, then waits for the new task while
     // its descriptor is fetched.  A worker in a POTRF pool takes the pool's
     // next sub-unit instead, and returns to the tickets when none is left.
     if (wave == 0) {
-      int task = -1, part = 0, unit = -1, t = 0;
+      int task = -1, part = 0, unit = -1, t = 0, failed = 0;
       bool claimed = false;
       uint64_t tw = 0;
       if (POOLED && pl_task >= 0) {
@@ -3047,7 +3280,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
           part = uniform_i(a.items[2 * t + 1]);
           if (a.trace) tw = wall_clock64();
           const int dv = lane < DESC_WORDS ? a.desc[DESC_WORDS * (int64_t)task + lane] : 0;
-          if (!wait_ready(a, task, lane)) task = -1;
+          if (!wait_ready(a, task, lane, one_failed, failed)) task = -1;
           if (lane < DESC_WORDS) s_desc[lane] = dv;
           const int kd = uniform_i(__builtin_amdgcn_readlane(dv, 0)), pd = uniform_i(__builtin_amdgcn_readlane(dv, 4));
           if (POOLED && task >= 0 && kd == TK_POTRF && pd > 1) {
@@ -3081,6 +3314,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         s_claim[1] = part;
         s_claim[2] = t;
         s_claim[3] = unit;
+        s_claim[4] = failed;
         if (a.trace && task >= 0 && !claimed) {
           a.trace[4 * (int64_t)t + 0] = tw;
           a.trace[4 * (int64_t)t + 1] = wall_clock64();
@@ -3099,7 +3333,17 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
     const int d_parts = uniform_i(s_desc[4]), d_e0 = uniform_i(s_desc[5]), d_e1 = uniform_i(s_desc[6]);
     // the task's system: base pointers, order, tile size, leading dimension
     const int sid = uniform_i(s_desc[7]);
-    const int64_t* sr = a.sys + SYS_WORDS * (int64_t)sid;
+    int64_t sr[SYS_WORDS];
+    if (one_matrix) {
+#pragma unroll
+      for (int i = 0; i < SYS_WORDS; ++i) {
+        const int64_t v = s_sys[SYS_WORDS * sid + i];
+        sr[i] = ((int64_t)uniform_i((int)(v >> 32)) << 32) | (int64_t)(uint32_t)uniform_i((int)v);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < SYS_WORDS; ++i) sr[i] = a.sys[SYS_WORDS * (int64_t)sid + i];
+    }
     using E = typename std::conditional<MIXED, float, double>::type;
     E* const Abase = reinterpret_cast<E*>(a.A) + sr[0];
     double* const Bbase = a.B + sr[1];
@@ -3118,7 +3362,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
     };
     // in a batched launch a system whose factorization failed only passes
     // its remaining tasks on, so that the DAG drains
-    const bool skip = a.batched && uniform_i(ld_relaxed(&a.sinfo[a.batched == 2 ? 0 : sid])) != 0;
+    const bool skip = one_matrix ? uniform_i(s_claim[4]) != 0 : a.batched && uniform_i(ld_relaxed(&a.sinfo[sid])) != 0;
     int ok = 1;
     // A unit of a POTRF pool runs the POTRF, TRSM or GEMM body on sub-blocks
     // of the diagonal tile (tk, tk): po_* give the sub-block offsets (rows,
