@@ -62,8 +62,9 @@ typedef struct KArgs {
   int32_t *pool;        /* POOL_WORDS counters per diagonal tile of every system
                            (the split POTRF's sub-unit pool), zeroed per launch */
   uint16_t *H;          /* BF16-update factorization: three BF16 terms of every panel
-                           tile, K-contiguous: column block k, row r, column c of
-                           term t at H[((t T + k) hrows + r) nb + c]             */
+                           tile, in blocks of 16 rows by 32 columns (1 KB, swizzled
+                           as their LDS image): of term t, column block k, row
+                           group g, columns 32 c .. at H + ((t T + k) hrows + 16 g) nb + 512 c */
   int64_t hrows;        /* rows per column block of H (T nb)                      */
   float *A32;           /* mode 7: the systems' FP32 matrices (system s at A32 +
                            sys word 5, leading dimension sys word 7), read for the

@@ -535,7 +535,9 @@ B32Layout b32_layout(std::vector<tchol::System>* sys, int64_t nrhs, const Plan& 
 // move four rows per 16-byte lane, so three rows past the order are read;
 // they hold zeros).
 // With BF16 updates the workspace also holds the panels' BF16 terms (H):
-// three terms, per column block T nb rows of nb K-contiguous values.
+// three terms, per column block T nb rows of nb values in blocks of 16 rows by
+// 32 columns, and after the last of them the 256 rows that a whole update item
+// starting at the last row block would read.
 struct MixedLayout {
   int64_t ldw = 0, w = 0, h = 0, hrows = 0, d = 0, dinv = 0, dinvt = 0, b0 = 0, r = 0, sx = 0, part = 0, norms = 0,
           sched = 0, end = 0;
@@ -548,7 +550,7 @@ MixedLayout mixed_layout(int64_t n, int64_t nb, int64_t nrhs, const Plan& fp, co
   M.w = 0;
   M.h = align_up(M.w + 4 * M.ldw * n);
   M.hrows = T * nb;
-  M.d = align_up(M.h + (bf16 ? 2 * 3 * T * M.hrows * nb : 0));
+  M.d = align_up(M.h + (bf16 ? 2 * (3 * T * M.hrows + 256) * nb : 0));
   M.dinv = align_up(M.d + 8 * T * nb * nb);        // L_kk^{-1} per diagonal tile (FP64)
   M.dinvt = align_up(M.dinv + 8 * T * nb * nb);    // L_kk^{-T}
   M.b0 = align_up(M.dinvt + 8 * T * nb * nb);

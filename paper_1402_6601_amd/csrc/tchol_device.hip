@@ -926,20 +926,30 @@ __device__ __forceinline__ void gemm_nt_f32_d(double* Cd, int64_t ldcd, const fl
 // ---------------------------------------------------------------------------
 // BF16 GEMM item of the BF16-update factorization: C[M x N] (FP32, ld ldc)
 // -= A B^T with A (M x K) and B (N x K) each given as three BF16 terms
-// (hi + mid + lo, split3) in K-contiguous rows (row stride hld, terms hterm
-// apart; K beyond one column block of kb columns continues in the next
-// block, hblk further); M <= 256, N <= 128, K % 32 == 0, kb % 32 == 0.  The six products of terms whose
-// orders add up to at most two (hh, hm, mh, mm, hl, lh) run on the BF16
-// matrix cores (v_mfma_f32_16x16x32_bf16) with FP32 accumulation; the
+// (hi + mid + lo, split3), M <= 256, N <= 128, K % 32 == 0.  The six products
+// of terms whose orders add up to at most two (hh, hm, mh, mm, hl, lh) run on
+// the BF16 matrix cores (v_mfma_f32_16x16x32_bf16) with FP32 accumulation; the
 // terms left out are below 2^-24 of the product, so the update keeps FP32
-// accuracy.  2 x 2 wavefronts of 128 x 64.  A chunk of 32 k holds, per
-// term, 64-byte rows of A (256) and B (128) in LDS, filled by direct
-// 16-byte transfers (16 rows per wavefront instruction); the four 16-byte
-// quarters of a row are XOR-swizzled by bits 2-3 of the row, so the
-// fragment reads of 16 consecutive rows hit distinct banks.  Two stages;
-// the next chunk's 72 transfers go out at the start of the current chunk's
-// products.  The instruction has no operand negation: the accumulators
-// start from -C and -acc is stored.
+// accuracy.
+//
+// The panels come in blocks of 1 KB, 16 rows by 32 columns of one term, laid
+// out as their LDS image (H_BLOCK: a row's four 16-byte quarters are
+// XOR-swizzled by bits 2-3 of the row, so the fragment reads of 16 consecutive
+// rows hit distinct banks); a row group's blocks follow each other along a
+// column block (nc of them), gs bytes from one row group to the next, hblk
+// from one column block to the next and hterm from one term to the next.  A
+// transfer is then one contiguous KB at a running scalar pointer, four
+// instructions in all: with the rows of a K-contiguous layout (64-byte pieces,
+// a 64-bit address per lane) the 18 transfers of a chunk took twice as long to
+// issue as its products to run.
+// 2 x 2 wavefronts of 128 x 64, chunks of 32 k in two LDS stages; what a chunk
+// issues besides its products goes between groups of four of them.  The
+// instruction has no operand negation: the accumulators start from -C and -acc
+// is stored (C at the end would round less, which changes how many refinement
+// steps a solve takes).
+// A whole item of K = 1024 with all 256 workgroups busy (n = 32768): 120 -> 88 us
+// (the products alone take 41 us; the panels' 2.4 MB then arrive at 6.9 TB/s
+// over the chip, mostly from beyond the L2s).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 #define BW_SLOTS_A 1024                               // 16-byte slots per term of A: 256 rows x 4
 #define BW_SLOTS_B 512                                // of B: 128 rows x 4
@@ -947,102 +957,146 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ int bw_slot(int row, int q) { return row * 4 + (q ^ ((row >> 2) & 3)); }
 
-__device__ __forceinline__ void gemm_bf16x6_wide(float* __restrict__ C, int64_t ldc, const uint16_t* __restrict__ Ha,
-                                                 const uint16_t* __restrict__ Hb, int64_t hld, int64_t hterm,
-                                                 int64_t hblk, int kb, int M, int N, int K, double* lds_d) {
+__device__ __forceinline__ void gemm_bf16x6_wide(float* __restrict__ C, int64_t ldc, const char* __restrict__ Ha,
+                                                 const char* __restrict__ Hb, int64_t gs, int64_t hterm, int64_t hblk,
+                                                 int nc, int M, int N, int K, double* lds_d) {
   constexpr int KC = 32;
   static_assert(2 * BW_STAGE_BYTES <= 8 * LDS_DOUBLES, "two stages must fit the workgroup LDS");
-  char* lds = reinterpret_cast<char*>(lds_d);
+  const char* const lds = reinterpret_cast<const char*>(lds_d);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int l16 = lane & 15, lg = lane >> 4;
 
   f4 acc[8][4];
-#pragma unroll
-  for (int rb = 0; rb < 8; ++rb)
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = wm * 128 + rb * 16 + l16, col = wn * 64 + cb * 16 + 4 * lg + i;
-        acc[rb][cb][i] = -C[(int64_t)imin(col, N - 1) * ldc + imin(row, M - 1)];
-      }
-  // transfer j (0..71) of chunk ch: A term j / 16, rows 16 (j % 16) ..; then B term (j - 48) / 8
-  auto xfer = [&](int ch, int j) __attribute__((always_inline)) {
-    char* st = lds + (ch & 1) * BW_STAGE_BYTES;
-    const bool isa = j < 48;
-    const int term = isa ? j >> 4 : (j - 48) >> 3, grp = isa ? j & 15 : (j - 48) & 7;
-    const int row = grp * 16 + (lane >> 2);
-    const int q = (lane & 3) ^ ((row >> 2) & 3);
-    const int kk = ch * KC;  // k of the chunk: column kk % kb of column block kk / kb
-    const uint16_t* g = (isa ? Ha : Hb) + term * hterm + (int64_t)(kk / kb) * hblk +
-                        (int64_t)imin(row, (isa ? M : N) - 1) * hld + kk % kb + 8 * q;
-    char* dst = st + (isa ? term * BW_SLOTS_A : 3 * BW_SLOTS_A + term * BW_SLOTS_B) * 16 + grp * 64 * 16;
-    dma16(g, reinterpret_cast<double*>(dst));
+  // this wavefront's transfers of a chunk: row groups wave, wave + 4, ... of A
+  // (four per term) and of B (two per term); groups past the panel read
+  // whatever follows (the workspace reserves it) for outputs never stored
+  const uint32_t off = 16u * (uint32_t)lane;
+  const uint32_t l0 = lds_addr(lds_d) + 1024u * (uint32_t)wave;
+  const uint64_t g4 = 4 * (uint64_t)gs, nta = (uint64_t)hterm - 3 * g4, ntb = (uint64_t)hterm - g4;
+  uint64_t qa = (uint64_t)(uintptr_t)uniform_ptr(Ha + wave * gs), qb = (uint64_t)(uintptr_t)uniform_ptr(Hb + wave * gs);
+  uint64_t pa = qa, pb = qb;  // running pointers within a chunk
+  int cleft = nc;             // chunks left in the column block
+  auto next_chunk = [&]() __attribute__((always_inline)) {
+    const uint64_t d = --cleft == 0 ? (uint64_t)hblk - 1024u * (uint64_t)(nc - 1) : 1024u;
+    if (cleft == 0) cleft = nc;
+    pa = qa += d;
+    pb = qb += d;
   };
-  auto issue = [&](int ch) __attribute__((always_inline)) {
-#pragma unroll
-    for (int jj = 0; jj < 18; ++jj) xfer(ch, wave + 4 * jj);
+  auto xfer = [&](auto jc, uint32_t st) __attribute__((always_inline)) {
+    constexpr int j = decltype(jc)::value;
+    if constexpr (j < 12) {
+      dma16i<(j / 4) * BW_SLOTS_A * 16 + (j % 4) * 4096>(pa, off, st);
+      pa += j % 4 == 3 ? nta : g4;
+    } else {
+      constexpr int k = j - 12;
+      dma16i<(3 * BW_SLOTS_A + (k / 2) * BW_SLOTS_B) * 16 + (k % 2) * 4096>(pb, off, st);
+      pb += k % 2 == 1 ? ntb : g4;
+    }
   };
-  auto compute = [&](int ch, int nx) __attribute__((always_inline)) {
-    const char* st = lds + (ch & 1) * BW_STAGE_BYTES;
-    if (nx >= 0) issue(nx);
-    bf16x8 fb[3][4];
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
+  const char* const fa0 = lds + bw_slot(wm * 128 + l16, lg) * 16;
+  const char* const fb0 = lds + (3 * BW_SLOTS_A + bw_slot(wn * 64 + l16, lg)) * 16;
+  // the products of the chunk in stage so (bytes), with the transfers of the
+  // next one into the stage at st
+  auto compute = [&](auto issue_c, int so, uint32_t st) __attribute__((always_inline)) {
+    constexpr bool ISSUE = decltype(issue_c)::value;
+    bf16x8 fb[3][4], fan[2][3];
+    auto read_a = [&](int rb, int t) __attribute__((always_inline)) {
+      fan[rb & 1][t] = *reinterpret_cast<const bf16x8*>(fa0 + so + (t * BW_SLOTS_A + rb * 64) * 16);
+    };
+    auto read_b = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb)
-        fb[t][cb] = *reinterpret_cast<const bf16x8*>(
-            st + (3 * BW_SLOTS_A + t * BW_SLOTS_B + bw_slot(wn * 64 + cb * 16 + l16, lg)) * 16);
-    // the A fragments of row block rb + 1 are read while the products of rb run
-    bf16x8 fan[2][3];
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-      fan[0][t] = *reinterpret_cast<const bf16x8*>(st + (t * BW_SLOTS_A + bw_slot(wm * 128 + l16, lg)) * 16);
-#pragma unroll
-    for (int rb = 0; rb < 8; ++rb) {
-      if (rb + 1 < 8) {
-#pragma unroll
-        for (int t = 0; t < 3; ++t)
-          fan[(rb + 1) & 1][t] = *reinterpret_cast<const bf16x8*>(
-              st + (t * BW_SLOTS_A + bw_slot(wm * 128 + (rb + 1) * 16 + l16, lg)) * 16);
-      }
-      const bf16x8* fa = fan[rb & 1];
+        fb[t][cb] = *reinterpret_cast<const bf16x8*>(fb0 + so + (t * BW_SLOTS_B + cb * 64) * 16);
+    };
+    // in the order of their first use
+    read_b(2);
+    read_a(0, 0);
+    read_b(0);
+    read_a(0, 2);
+    read_b(1);
+    read_a(0, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<8>([&](auto rc) __attribute__((always_inline)) {
+      constexpr int rb = decltype(rc)::value;
       // term pairs (B term, A term) from the smallest: h l, l h, m m, h m, m h, h h;
       // consecutive instructions go to the four independent accumulators
       // of the row block, so none waits for the previous one's result
-      constexpr int PB[6] = {2, 0, 1, 1, 0, 0}, PA[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-      for (int pr = 0; pr < 6; ++pr)
+      static_for<6>([&](auto pc) __attribute__((always_inline)) {
+        constexpr int pr = decltype(pc)::value;
+        constexpr int PB[6] = {2, 0, 1, 1, 0, 0}, PA[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb)
-          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[PB[pr]][cb], fa[PA[pr]], acc[rb][cb], 0, 0, 0);
-    }
+          acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[PB[pr]][cb], fan[rb & 1][PA[pr]], acc[rb][cb], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (pr < 3) {
+          constexpr int T[3] = {0, 2, 1};
+          if constexpr (rb + 1 < 8) read_a(rb + 1, T[pr]);
+        } else if constexpr (ISSUE && rb < 6) {
+          xfer(std::integral_constant<int, 3 * rb + pr - 3>(), st);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
   };
   const int nch = K / KC;
-  if (nch > 0) {
-    issue(0);
-    wait_vmcnt<0>();  // the loads of C and chunk 0
-    __syncthreads();
-    for (int ch = 0; ch < nch; ++ch) {
-      compute(ch, ch + 1 < nch ? ch + 1 : -1);
-      if (ch + 1 < nch) {
-        wait_vmcnt<0>();
-        __syncthreads();
-      }
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int rb = 0; rb < 8; ++rb)
+  static_for<18>([&](auto jc) __attribute__((always_inline)) { xfer(jc, l0); });
+  // C: of a whole tile, one pointer per column of a lane and constant row offsets
+  const bool whole = M == 256 && N == 128;
+  float* const Cl = C + (int64_t)(wn * 64 + 4 * lg) * ldc + wm * 128 + l16;
+  if (whole) {
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int row = wm * 128 + rb * 16 + l16, col = wn * 64 + cb * 16 + 4 * lg + i;
-        if (row < M && col < N) st_dev(C + (int64_t)col * ldc + row, -acc[rb][cb][i]);
+        const float* const q = Cl + (int64_t)(cb * 16 + i) * ldc;
+#pragma unroll
+        for (int rb = 0; rb < 8; ++rb) acc[rb][cb][i] = -q[rb * 16];
       }
+  } else {
+#pragma unroll
+    for (int rb = 0; rb < 8; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = wm * 128 + rb * 16 + l16, col = wn * 64 + cb * 16 + 4 * lg + i;
+          acc[rb][cb][i] = -C[(int64_t)imin(col, N - 1) * ldc + imin(row, M - 1)];
+        }
+  }
+  wait_vmcnt<0>();
+  lds_barrier();
+  int so = 0;
+  for (int ch = 0; ch + 1 < nch; ++ch) {
+    next_chunk();
+    compute(std::true_type(), so, l0 + (uint32_t)(BW_STAGE_BYTES - so));
+    so = BW_STAGE_BYTES - so;
+    wait_vmcnt<0>();
+    lds_barrier();
+  }
+  compute(std::false_type(), so, 0);
+  lds_barrier();
+  if (whole) {
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float* const q = Cl + (int64_t)(cb * 16 + i) * ldc;
+#pragma unroll
+        for (int rb = 0; rb < 8; ++rb) st_dev(q + rb * 16, -acc[rb][cb][i]);
+      }
+  } else {
+#pragma unroll
+    for (int rb = 0; rb < 8; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = wm * 128 + rb * 16 + l16, col = wn * 64 + cb * 16 + 4 * lg + i;
+          if (row < M && col < N) st_dev(C + (int64_t)col * ldc + row, -acc[rb][cb][i]);
+        }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1826,13 +1880,15 @@ __device__ __forceinline__ int potrf_tile(double* __restrict__ Akk, int64_t ld, 
 // inverse of the mixed-precision solve, from identity strips.
 #define TS 32
 
-// Hs (non-null): the solved strip is also stored as three BF16 terms
-// (split3) in K-contiguous rows: strip row r, column c of term t at
-// Hs[t * hterm + r * hld + c] (the BF16 panels of the BF16-update factorization).
+// Hs (non-null): the solved strip (its first row a multiple of 16 in the
+// matrix) is also stored as three BF16 terms (split3) in the 1 KB blocks of
+// gemm_bf16x6_wide: Hs is the block of the strip's first row and column, a
+// row group's blocks follow each other, the next row group is hgs and the next
+// term hterm values further (mk a multiple of 32).
 template <typename TX, int REV = 0>
 __device__ __forceinline__ void trsm_strip(TX* __restrict__ X, int64_t ldx, const double* __restrict__ Lkk, int64_t ld,
                                            int S, int mk, double* lds, double* Qb = nullptr,
-                                           int64_t ldq = 0, uint16_t* Hs = nullptr, int64_t hld = 0,
+                                           int64_t ldq = 0, uint16_t* Hs = nullptr, int64_t hgs = 0,
                                            int64_t hterm = 0) {
   double* Xs = lds;  // [2][512][16]
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1958,7 +2014,7 @@ __device__ __forceinline__ void trsm_strip(TX* __restrict__ X, int64_t ldx, cons
     // runs of 4 columns (8 bytes per term): lane l of wavefront w takes row
     // 16 (w & 1) + l % 16 (consecutive rows: conflict-free reads of Xs) and
     // runs 4 u + l / 16 of its half of the columns (w / 2); a store
-    // instruction then writes 32-byte pieces of 16 rows
+    // instruction then writes half of a 1 KB block
     const int hr = 16 * (wave & 1) + l16, half = mk >> 3;  // runs of 4 per half of the columns
     if (hr < S) {
 #pragma unroll 1
@@ -1973,7 +2029,7 @@ __device__ __forceinline__ void trsm_strip(TX* __restrict__ X, int64_t ldx, cons
           t1 |= (uint64_t)a1 << (16 * e);
           t2 |= (uint64_t)a2 << (16 * e);
         }
-        uint16_t* h = Hs + (int64_t)hr * hld + c0;
+        uint16_t* h = Hs + (int64_t)(wave & 1) * hgs + (int64_t)(c0 >> 5) * 512 + bw_slot(l16, (c0 >> 3) & 3) * 8 + (c0 & 7);
         st_dev(reinterpret_cast<uint64_t*>(h), t0);
         st_dev(reinterpret_cast<uint64_t*>(h + hterm), t1);
         st_dev(reinterpret_cast<uint64_t*>(h + 2 * hterm), t2);
@@ -3469,9 +3525,10 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
           } else {
             const int r0 = part * a.trsm_rows;
             const int S = imin(a.trsm_rows, tsz(ti) - r0);
-            if constexpr (MODE == 5)  // the strip also as BF16 terms, for the BF16 updates
+            if constexpr (MODE == 5)  // the strip also as BF16 terms, for the BF16 updates (whole 32-column blocks)
               trsm_strip(Abase + (tk * nb) * ld + ti * nb + r0, ld, Dk, nb, S, tsz(tk), lds, nullptr, 0,
-                         a.H + ((int64_t)tk * a.hrows + (int64_t)ti * nb + r0) * nb, nb, (int64_t)a.T * a.hrows * nb);
+                         nb % 32 == 0 ? a.H + ((int64_t)tk * a.hrows + (int64_t)ti * nb + r0) * nb : nullptr, 16 * nb,
+                         (int64_t)a.T * a.hrows * nb);
             else
               trsm_strip(Abase + (tk * nb) * ld + ti * nb + r0, ld, Dk, nb, S, tsz(tk), lds);
           }
@@ -3559,8 +3616,9 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
             gemm_nt_f32_d(Dsys + (int64_t)ti * nb * nb + (int64_t)(sj * bn) * nb + si * bm, nb, Ap, Bp, ld, M, N,
                           tsz(tk), si == sj, lds);
           else if (MODE == 5 && bm == 256 && bn == 128 && tsz(tk) % 32 == 0)
-            gemm_bf16x6_wide(C, ld, a.H + ((int64_t)tk * a.hrows + crow) * nb, a.H + ((int64_t)tk * a.hrows + brow) * nb,
-                             nb, (int64_t)a.T * a.hrows * nb, a.hrows * nb, (int)nb, M, N, K, lds);
+            gemm_bf16x6_wide(C, ld, (const char*)(a.H + ((int64_t)tk * a.hrows + crow) * nb),
+                             (const char*)(a.H + ((int64_t)tk * a.hrows + brow) * nb), 32 * nb,
+                             2 * (int64_t)a.T * a.hrows * nb, 2 * a.hrows * nb, (int)nb / 32, M, N, K, lds);
           else if (bm == 256 && bn == 128 && tsz(tk) % 32 == 0)
             gemm_f32_wide<32, 3>(C, Ap, Bp, ld, M, N, K, lds);
           else  // 128-row products (a 256-row item whose K is not a multiple of 32 takes two)
