@@ -28,6 +28,7 @@
 
 #define NT 256                 // threads per workgroup: 4 wavefronts of 64
 #define LDS_DOUBLES 20352      // 162816 bytes of LDS per workgroup (gfx950 allows 163840)
+#define LDS_COMPACT_DOUBLES 10112  // of the compact instance, two workgroups per compute unit
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
@@ -359,17 +360,12 @@ __device__ __forceinline__ void gemm_kloop(d4 (&acc)[RB][CB], const double* __re
   }
 }
 
-// ldc: leading dimension of C when it differs from the panels' (< 0: ld);
-// zero_c: start from C = 0 instead of loading C; ldb: the B panel's leading
-// dimension when it differs from A's (< 0: ld); neg: store -C.  CF32: the
-// initial C is read from the FP32 matrix Cf (leading dimension ldcf) instead.
-template <int SEG, int BM, int BN, int KC, int WGM, int NST, int PAD = 8, bool CF32 = false>
-__device__ __forceinline__ void gemm_core(double* __restrict__ C, const double* __restrict__ Ap,
-                                          const double* __restrict__ Bp, int64_t ld, int M, int N, int K,
-                                          bool lower_only, double* lds, double* Cl = nullptr, int ldl = 0,
-                                          int64_t ldc = -1, bool zero_c = false, int64_t ldb = -1,
-                                          bool neg = false, const float* __restrict__ Cf = nullptr,
-                                          int64_t ldcf = 0) {
+// ldc: leading dimension of C when it differs from the panels' (< 0: ld).  The
+// result goes to LDS at Cl (column-major, leading dimension ldl).
+template <int SEG, int BM, int BN, int KC, int WGM, int NST, int PAD>
+__device__ __forceinline__ void gemm_core(const double* __restrict__ C, const double* __restrict__ Ap,
+                                          const double* __restrict__ Bp, int64_t ld, int M, int N, int K, double* lds,
+                                          double* Cl, int ldl, int64_t ldc = -1) {
   const int64_t ldC = ldc < 0 ? ld : ldc;
   using S = GemmShape<BM, BN, KC, WGM, NST, PAD>;
   constexpr int RB = S::RB, CB = S::CB;
@@ -386,13 +382,10 @@ __device__ __forceinline__ void gemm_core(double* __restrict__ C, const double* 
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = wm * S::WTM + rb * 16 + l16, col = wn * S::WTN + cb * 16 + 4 * i + lg;
-        if constexpr (CF32)
-          acc[rb][cb][i] = (double)Cf[(int64_t)imin(col, N - 1) * ldcf + imin(row, M - 1)];
-        else
-          acc[rb][cb][i] = zero_c ? 0.0 : C[(int64_t)imin(col, N - 1) * ldC + imin(row, M - 1)];
+        acc[rb][cb][i] = C[(int64_t)imin(col, N - 1) * ldC + imin(row, M - 1)];
       }
 
-  gemm_kloop<BM, BN, KC, WGM, NST, PAD, SEG>(acc, Ap, Bp, ld, M, N, K, lds, ldb);
+  gemm_kloop<BM, BN, KC, WGM, NST, PAD, SEG>(acc, Ap, Bp, ld, M, N, K, lds);
   __syncthreads();  // every wavefront is done with the stages before LDS is reused
 
 #pragma unroll
@@ -402,13 +395,7 @@ __device__ __forceinline__ void gemm_core(double* __restrict__ C, const double* 
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = wm * S::WTM + rb * 16 + l16, col = wn * S::WTN + cb * 16 + 4 * i + lg;
-        if (row < M && col < N && (!lower_only || row >= col)) {
-          const double v = neg ? -acc[rb][cb][i] : acc[rb][cb][i];
-          if (Cl)
-            Cl[col * ldl + row] = v;  // result kept in LDS (column-major, ld ldl)
-          else
-            st_dev(C + (int64_t)col * ldC + row, v);
-        }
+        if (row < M && col < N) Cl[col * ldl + row] = acc[rb][cb][i];
       }
 }
 
@@ -1666,78 +1653,44 @@ __device__ __forceinline__ int potrf_small(double* __restrict__ Akk, int64_t ld,
 // Panels of 32 columns halve the number of panels and the re-reads of the
 // factored columns relative to the 16 of the diagonal blocks, and give the
 // updates enough outputs per K step to keep the matrix cores busy.
-// SLAB = 128: slabs of 128 rows in a compact layout of 81024 bytes (two
-// workgroups per compute unit): L_dd and the reciprocal pivots live in the
-// update's staging area (free once the product is in the slab), the columns
-// of L_dd below the diagonal packed.  With Bf (compact layout only) the
-// forward solve L y = b of nrhs <= 4 right-hand sides (column-major at Bf,
-// leading dimension ldbf) rides along, right-looking by panels: in the first
-// slab of a panel, thread 128 + j solves the panel's rows of column j
-// against L_dd (the same substitution as the rows below the block, on the
-// values the earlier panels left) and stores them, final, to Bf and to Yp;
-// when a slab is stored, each of its rows below the block takes
-// b -= L(row, panel) y_panel.  Bf then holds y.
 // Returns 0, or the 1-based column (within the tile) whose pivot is not
 // positive (zero, negative or NaN).
 #define PT_W 32
 #define PT_SLAB 256
 #define PT_LT 36                               // stride of the columns of L_dd
-#define PT_LT_PACKED (PT_W * (PT_W + 1) / 2)   // the packed columns (c2 >= c)
-#define PT_FWD 4                               // right-hand sides of the fused forward solve
-#define PT_LDS_COMPACT (2 * 16 * (128 + PT_W) + PT_W * 136 + PT_LT_PACKED + PT_W * PT_FWD)
-#define FRB_COMPACT_DOUBLES (32 * 4 * 64 + 2 * 4 * 64)  // tile_solve<true>
 
-// IN32 (compact layout): the tile's values are read from the FP32 matrix A32
-// (leading dimension ld32) instead of Akk, and L is written to both (Akk in
-// FP64 for the later panels' products, A32 rounded to FP32).
-template <int SEG, int SLAB = PT_SLAB, bool IN32 = false>
-__device__ __forceinline__ int potrf_tile(double* __restrict__ Akk, int64_t ld, int m, double* lds,
-                                          double* Bf = nullptr, int64_t ldbf = 0, int nrhs = 0,
-                                          float* __restrict__ A32 = nullptr, int64_t ld32 = 0) {
-  static_assert(!IN32 || SLAB == 128, "FP32 input in the compact layout only");
-  static_assert(SLAB == 256 || SLAB == 128, "slab height");
-  constexpr bool PACKED = SLAB < PT_SLAB;
-  constexpr int LDP = SLAB + 8;                        // LDS leading dimension of a slab
-  constexpr int STAGE = 2 * 16 * (SLAB + PT_W);        // stages of gemm_core<SEG, SLAB, 32, 16, 4, 2, 0>
-  static_assert(PACKED ? (STAGE + PT_W * LDP + PT_LT_PACKED + PT_W * PT_FWD == PT_LDS_COMPACT &&
-                          PT_W * (PT_W + 1) + PT_W <= STAGE)
-                       : STAGE + PT_W * LDP + PT_W * (PT_W + 1) + PT_W + PT_W * PT_LT <= LDS_DOUBLES,
-                "LDS budget");
+template <int SEG>
+__device__ __forceinline__ int potrf_tile(double* __restrict__ Akk, int64_t ld, int m, double* lds) {
+  constexpr int LDP = PT_SLAB + 8;                     // LDS leading dimension of a slab
+  constexpr int STAGE = 2 * 16 * (PT_SLAB + PT_W);     // stages of gemm_core<SEG, PT_SLAB, 32, 16, 4, 2, 0>
+  static_assert(STAGE + PT_W * LDP + PT_W * (PT_W + 1) + PT_W + PT_W * PT_LT <= LDS_DOUBLES, "LDS budget");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  double* Ps = lds + STAGE;                                 // [PT_W][LDP] the slab
-  double* Ldd = PACKED ? lds : Ps + PT_W * LDP;             // [PT_W][PT_W + 1] the diagonal block (lower)
-  double* Linv = Ldd + PT_W * (PT_W + 1);                   // [PT_W] reciprocal pivots
-  double* LT = PACKED ? Ps + PT_W * LDP : Linv + PT_W;      // L_dd by columns
-  double* Yp = LT + PT_LT_PACKED;                           // [PT_W][PT_FWD] the panel's rows of y (Bf)
-  const bool fwd = PACKED && Bf != nullptr;
-  // column c of L_dd from its diagonal down (c2 >= c): LT[lt(c) + c2]
-  auto lt = [](int c) __attribute__((always_inline)) { return PACKED ? c * PT_W - c * (c + 1) / 2 : c * PT_LT; };
+  double* Ps = lds + STAGE;                 // [PT_W][LDP] the slab
+  double* Ldd = Ps + PT_W * LDP;            // [PT_W][PT_W + 1] the diagonal block (lower)
+  double* Linv = Ldd + PT_W * (PT_W + 1);   // [PT_W] reciprocal pivots
+  double* LT = Linv + PT_W;                 // L_dd by columns: column c at LT[c * PT_LT + c2]
   __shared__ int s_info;
   for (int c0 = 0; c0 < m; c0 += PT_W) {
     const int w = imin(PT_W, m - c0);
     const int R = m - c0;
     double* P = Akk + (int64_t)c0 * ld + c0;
-    float* const P32 = IN32 ? A32 + (int64_t)c0 * ld32 + c0 : nullptr;
-    for (int s0 = 0; s0 < R; s0 += SLAB) {
-      const int S = imin(SLAB, R - s0);
+    for (int s0 = 0; s0 < R; s0 += PT_SLAB) {
+      const int S = imin(PT_SLAB, R - s0);
       if (c0 > 0) {
         // the slab - L[c0 + s0 :, 0 : c0] L[c0 : c0 + w, 0 : c0]^T into LDS,
         // on a product no taller than the slab needs
-        if (SLAB > 128 && S > 128)
-          gemm_core<SEG, SLAB, PT_W, 16, 4, 2, 0, IN32>(P + s0, Akk + c0 + s0, Akk + c0, ld, S, w, c0, false, lds, Ps,
-                                                        LDP, -1, false, -1, false, IN32 ? P32 + s0 : nullptr, ld32);
+        if (S > 128)
+          gemm_core<SEG, PT_SLAB, PT_W, 16, 4, 2, 0>(P + s0, Akk + c0 + s0, Akk + c0, ld, S, w, c0, lds, Ps, LDP);
         else if (S > 64)
-          gemm_core<SEG, 128, PT_W, 16, 4, 2, 0, IN32>(P + s0, Akk + c0 + s0, Akk + c0, ld, S, w, c0, false, lds, Ps,
-                                                       LDP, -1, false, -1, false, IN32 ? P32 + s0 : nullptr, ld32);
+          gemm_core<SEG, 128, PT_W, 16, 4, 2, 0>(P + s0, Akk + c0 + s0, Akk + c0, ld, S, w, c0, lds, Ps, LDP);
         else
-          gemm_core<SEG, 64, PT_W, 16, 4, 2, 0, IN32>(P + s0, Akk + c0 + s0, Akk + c0, ld, S, w, c0, false, lds, Ps,
-                                                      LDP, -1, false, -1, false, IN32 ? P32 + s0 : nullptr, ld32);
+          gemm_core<SEG, 64, PT_W, 16, 4, 2, 0>(P + s0, Akk + c0 + s0, Akk + c0, ld, S, w, c0, lds, Ps, LDP);
       } else if (tid < S) {
         double v[PT_W];
 #pragma unroll
         for (int c = 0; c < PT_W; ++c)
-          v[c] = IN32 ? (double)P32[(int64_t)imin(c, w - 1) * ld32 + s0 + tid] : P[(int64_t)imin(c, w - 1) * ld + s0 + tid];
+          v[c] = P[(int64_t)imin(c, w - 1) * ld + s0 + tid];
 #pragma unroll
         for (int c = 0; c < PT_W; ++c) Ps[c * LDP + tid] = v[c];
       }
@@ -1777,49 +1730,32 @@ __device__ __forceinline__ int potrf_tile(double* __restrict__ Akk, int64_t ld, 
         // (c2 > c), the reciprocal pivot at c2 = c
         for (int idx = tid; idx < PT_W * PT_W; idx += NT) {
           const int c = idx / PT_W, c2 = idx - c * PT_W;
-          if (!PACKED || c2 >= c) LT[lt(c) + c2] = c2 == c ? Linv[c] : (c2 > c ? Ldd[c2 * (PT_W + 1) + c] : 0.0);
+          LT[c * PT_LT + c2] = c2 == c ? Linv[c] : (c2 > c ? Ldd[c2 * (PT_W + 1) + c] : 0.0);
         }
         __syncthreads();
       }
       // rows below the diagonal block: y := y L_dd^{-T}, one row per thread
       // (there are such rows only when the panel is 32 wide); each column's
-      // entries of L_dd are loaded together before they are used.  With Bf,
-      // threads 128 + j of the first slab take the panel's rows of column j
-      // of b (rows of the compact slab never reach thread 128)
+      // entries of L_dd are loaded together before they are used
       {
         const int r = (s0 == 0 ? w : 0) + tid;
-        const int j = tid - 128;
-        const bool rhs = fwd && s0 == 0 && j >= 0 && j < nrhs;
-        if (r < S || rhs) {
+        if (r < S) {
           double y[PT_W];
-          if (rhs) {
 #pragma unroll
-            for (int c = 0; c < PT_W; ++c) y[c] = c < w ? Bf[(int64_t)j * ldbf + c0 + c] : 0.0;
-          } else {
-#pragma unroll
-            for (int c = 0; c < PT_W; ++c) y[c] = Ps[c * LDP + r];
-          }
+          for (int c = 0; c < PT_W; ++c) y[c] = Ps[c * LDP + r];
 #pragma unroll
           for (int c = 0; c < PT_W; ++c) {
             double l[PT_W];
 #pragma unroll
-            for (int c2 = c; c2 < PT_W; ++c2) l[c2] = LT[lt(c) + c2];
+            for (int c2 = c; c2 < PT_W; ++c2) l[c2] = LT[c * PT_LT + c2];
 #pragma unroll
             for (int c2 = c; c2 < PT_W; ++c2) asm volatile("" : : "v"(l[c2]));
             y[c] *= l[c];
 #pragma unroll
             for (int c2 = c + 1; c2 < PT_W; ++c2) y[c2] -= y[c] * l[c2];
           }
-          if (rhs) {
 #pragma unroll
-            for (int c = 0; c < PT_W; ++c) {
-              Yp[c * PT_FWD + j] = y[c];
-              if (c < w) st_dev(Bf + (int64_t)j * ldbf + c0 + c, y[c]);
-            }
-          } else {
-#pragma unroll
-            for (int c = 0; c < PT_W; ++c) Ps[c * LDP + r] = y[c];
-          }
+          for (int c = 0; c < PT_W; ++c) Ps[c * LDP + r] = y[c];
         }
       }
       __syncthreads();
@@ -1828,28 +1764,7 @@ __device__ __forceinline__ int potrf_tile(double* __restrict__ Akk, int64_t ld, 
       if (tid < S) {
 #pragma unroll
         for (int c = 0; c < PT_W; ++c)
-          if (c < w && s0 + tid >= c) {
-            st_dev(P + (int64_t)c * ld + s0 + tid, Ps[c * LDP + tid]);
-            if constexpr (IN32) st_dev(P32 + (int64_t)c * ld32 + s0 + tid, (float)Ps[c * LDP + tid]);
-          }
-        if (fwd && s0 + tid >= w) {
-          // b(row) -= L(row, panel) y_panel for the rows below the block
-          double* const bp = Bf + c0 + s0 + tid;
-          double bv[PT_FWD];
-#pragma unroll
-          for (int jj = 0; jj < PT_FWD; ++jj) bv[jj] = jj < nrhs ? bp[(int64_t)jj * ldbf] : 0.0;
-#pragma unroll
-          for (int c = 0; c < PT_W; ++c) {
-            if (c < w) {
-              const double lv = Ps[c * LDP + tid];
-#pragma unroll
-              for (int jj = 0; jj < PT_FWD; ++jj) bv[jj] -= lv * Yp[c * PT_FWD + jj];
-            }
-          }
-#pragma unroll
-          for (int jj = 0; jj < PT_FWD; ++jj)
-            if (jj < nrhs) st_dev(bp + (int64_t)jj * ldbf, bv[jj]);
-        }
+          if (c < w && s0 + tid >= c) st_dev(P + (int64_t)c * ld + s0 + tid, Ps[c * LDP + tid]);
       }
       __syncthreads();
     }
@@ -1857,6 +1772,288 @@ __device__ __forceinline__ int potrf_tile(double* __restrict__ Akk, int64_t ld, 
     // update reads it
     wait_vmcnt<0>();
     __syncthreads();
+  }
+  return 0;
+}
+
+// ---------------------------------------------------------------------------
+// POTRF of a tile of order m on one workgroup of the compact instance (two per
+// compute unit: 256 registers, half the LDS).  Left-looking by panels of
+// PT_W = 32 columns in slabs of 128 rows that stay in registers from their
+// update to their store; wavefront w holds rows 32 w .. of the slab as 2 x 2
+// blocks of 16 x 16:
+//  1. the matrix cores apply every earlier column (panels streamed through two
+//     LDS stages of 16 columns as in gemm_tile);
+//  2. in the first slab, wavefront 0, which holds the 32 x 32 diagonal block,
+//     factors it in registers (panel16 on either half, the sub-steps' operands
+//     to LDS);
+//  3. every wavefront solves its rows below the block with those operands, on
+//     the matrix cores, and stores them from registers.
+// Slabs in LDS with one thread per row solving and storing (which this
+// replaces) spent as long outside the update as in it.  4096 systems of orders
+// 16 .. 512 in FP64, 4 right-hand sides: 4.75 -> 3.81 ms, mean POTRF 473 -> 347
+// us; of an order near 500 (1186 -> 914 us, two workgroups per compute unit)
+// now 680 in the update, whose panels are re-read from beyond the L2s, 120
+// in the diagonal blocks, 81 in the rows below.  Three stages instead of two
+// were slower (4.12 ms), as was swapping the halves of odd k-rows for them.
+// With Bf the forward solve L y = b of nrhs <= 4 right-hand sides
+// (column-major at Bf, leading dimension ldbf) rides along: a panel's rows of
+// b, transposed, are one more row block for step 3 (wavefront 0), and the rows
+// below take b -= L(row, panel) y_panel by products of the blocks they hold.
+// Bf then holds y.
+// IN32: the tile's values are read from the FP32 matrix A32 (leading
+// dimension ld32) instead of Akk, and L is written to both (Akk in FP64 for the
+// later panels' products, A32 rounded to FP32).
+// Needs an even ld, a 16-byte aligned tile and, for odd m, a readable row after
+// the last.  Returns 0, or the 1-based column (within the tile) whose pivot is
+// not positive (zero, negative or NaN).
+#define PT_FWD 4                               // right-hand sides of the fused forward solve
+#define PT_ALD 144                             // LDS stride of a staged k-row of the slab's panel
+#define PT_STAGE (16 * PT_ALD + 16 * PT_W)     // doubles of a stage
+#define PT_NST 2
+#define PT_LDS_COMPACT (PT_NST * PT_STAGE + 2 * QUAD_OPS * 64 + 4 * 64 + 8 * 64)
+#define FRB_COMPACT_DOUBLES (32 * 4 * 64 + 2 * 4 * 64)  // tile_solve<true>
+
+template <bool IN32>
+__device__ __forceinline__ int potrf_slabs(double* __restrict__ Akk, int64_t ld, int m, double* lds,
+                                           double* Bf, int64_t ldbf, int nrhs, float* __restrict__ A32, int64_t ld32) {
+  double* const Fb = lds + PT_NST * PT_STAGE;       // [2][QUAD_OPS][64] the halves' operands
+  double* const Xb = Fb + 2 * QUAD_OPS * 64;   // [4][64] the block below the first half's
+  double* const Yb = Xb + 4 * 64;              // [8][64] the panel's rows of y, as operands
+  __shared__ int s_pinfo;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
+  const bool fwd = Bf != nullptr;
+  double e[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) e[c] = (lg == c) ? 1.0 : 0.0;
+  const uint32_t l0 = lds_addr(lds);
+  const double* const fa0 = lds + lg * PT_ALD + wave * 32 + l16;
+  const double* const fb0 = lds + 16 * PT_ALD + lg * PT_W + l16;
+#pragma unroll 1
+  for (int c0 = 0; c0 < m; c0 += PT_W) {
+    const int w = imin(PT_W, m - c0), R = m - c0;
+    double* const P = Akk + (int64_t)c0 * ld + c0;
+    float* const P32 = IN32 ? A32 + (int64_t)c0 * ld32 + c0 : nullptr;
+#pragma unroll 1
+    for (int s0 = 0; s0 < R; s0 += 128) {
+      const int S = imin(128, R - s0);
+      const int rw = wave * 32;
+      const bool mine = rw < S;  // this wavefront has rows
+      d4 acc[2][2];
+      {
+        const int ra = imin(rw + l16, S - 1), rz = imin(rw + 16 + l16, S - 1) - ra;
+        if (w == PT_W) {
+          const double* const q = P + (int64_t)lg * ld + s0 + ra;
+          const float* const q32 = IN32 ? P32 + (int64_t)lg * ld32 + s0 + ra : nullptr;
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              acc[0][cb][i] = IN32 ? (double)q32[(int64_t)(cb * 16 + 4 * i) * ld32] : q[(int64_t)(cb * 16 + 4 * i) * ld];
+              acc[1][cb][i] =
+                  IN32 ? (double)q32[(int64_t)(cb * 16 + 4 * i) * ld32 + rz] : q[(int64_t)(cb * 16 + 4 * i) * ld + rz];
+            }
+        } else {
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int64_t col = imin(cb * 16 + 4 * i + lg, w - 1);
+              acc[0][cb][i] = IN32 ? (double)P32[col * ld32 + s0 + ra] : P[col * ld + s0 + ra];
+              acc[1][cb][i] = IN32 ? (double)P32[col * ld32 + s0 + ra + rz] : P[col * ld + s0 + ra + rz];
+            }
+        }
+      }
+      if (c0 > 0) {
+        // rows c0 + s0 .. and c0 .. of the earlier columns
+        const uint32_t offa = (uint32_t)(imin(2 * lane, (S - 1) & ~1) * 8);
+        const uint32_t offb = (uint32_t)(((int64_t)(lane >> 4) * ld + imin(2 * (lane & 15), (w - 1) & ~1)) * 8);
+        uint64_t pa = (uint64_t)(uintptr_t)uniform_ptr(Akk + (int64_t)wave * ld + c0 + s0);
+        uint64_t pb = (uint64_t)(uintptr_t)uniform_ptr(Akk + (int64_t)(4 * wave) * ld + c0);
+        const uint64_t da = 32 * (uint64_t)ld, db = 4 * da;
+        auto slot = [&](auto jc, uint32_t st) __attribute__((always_inline)) {
+          constexpr int j = decltype(jc)::value;
+          if constexpr (j < 4) {
+            dma16i<j * 4 * PT_ALD * 8>(pa, offa, st + (uint32_t)(wave * PT_ALD * 8));
+            pa += da;
+          } else {
+            dma16i<16 * PT_ALD * 8>(pb, offb, st + (uint32_t)(wave * 1024));
+            pb += db;
+          }
+        };
+        auto compute = [&](auto issue_c, int so, uint32_t st) __attribute__((always_inline)) {
+          constexpr bool ISSUE = decltype(issue_c)::value;
+          double fa[2][2], fb[2][2];
+          auto read = [&](int ks, int buf) __attribute__((always_inline)) {
+            fa[buf][0] = fa0[so + ks * 4 * PT_ALD];
+            fa[buf][1] = fa0[so + ks * 4 * PT_ALD + 16];
+            fb[buf][0] = fb0[so + ks * 4 * PT_W];
+            fb[buf][1] = fb0[so + ks * 4 * PT_W + 16];
+          };
+          // (all at once: the other workgroup's products run meanwhile, and the
+          // panels come from beyond the L2s more often than not)
+          if constexpr (ISSUE) static_for<5>([&](auto jc) __attribute__((always_inline)) { slot(jc, st); });
+          read(0, 0);
+          static_for<4>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int ks = decltype(kc)::value;
+            if constexpr (ks < 3) read(ks + 1, (ks + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (mine) {
+#pragma unroll
+              for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+                  acc[rb][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[ks & 1][cb], fa[ks & 1][rb], acc[rb][cb], 0, 0, 2 /* neg B */);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            
+          });
+        };
+        const int nch = c0 >> 4;  // even
+        static_for<5>([&](auto jc) __attribute__((always_inline)) { slot(jc, l0); });
+        int so = 0;
+#pragma unroll 1
+        for (int ch = 0; ch + 1 < nch; ++ch) {
+          wait_vmcnt<0>();
+          lds_barrier();
+          compute(std::true_type(), so, l0 + (uint32_t)(PT_STAGE - so) * 8);
+          so = PT_STAGE - so;
+        }
+        wait_vmcnt<0>();
+        lds_barrier();
+        compute(std::false_type(), so, 0);
+      }
+      if (s0 == 0) {
+        if (wave == 0) {
+          // the diagonal block: rows and columns past the order are the identity's
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int cb = 0; cb <= rb; ++cb)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const int r = rb * 16 + l16, c = cb * 16 + 4 * i + lg;
+                acc[rb][cb][i] = (r < w && c < w && r >= c) ? acc[rb][cb][i] : (r == c ? 1.0 : 0.0);
+              }
+          d4 y[2][1];  // the panel's rows of b, transposed
+          if (fwd) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const int c = h * 16 + 4 * i + lg;
+                const double v = Bf[(int64_t)imin(l16, nrhs - 1) * ldbf + c0 + imin(c, w - 1)];
+                y[h][0][i] = c < w ? v : 0.0;
+              }
+          }
+          d4 lf, ld2, none = {0.0, 0.0, 0.0, 0.0};
+          d4& x = acc[1][0];
+          const int ia = panel16(acc[0][0], lf, x, e, lane, c0, Fb);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[k], x[k], acc[1][1], 0, 0, 2 /* neg B */);
+            Xb[k * 64 + lane] = x[k];
+          }
+          const int ib = panel16(acc[1][1], ld2, none, e, lane, c0 + 16, Fb + QUAD_OPS * 64);
+          if (lane == 0) s_pinfo = ia ? ia : ib;
+          if (fwd) {
+            panel16_rows(y[0], Fb, lane);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              y[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[k], y[0][0][k], y[1][0], 0, 0, 2 /* neg B */);
+            panel16_rows(y[1], Fb + QUAD_OPS * 64, lane);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+              for (int k = 0; k < 4; ++k) Yb[(4 * h + k) * 64 + lane] = quad_to_row<0>(y[h][0][k]);
+          }
+          lds_barrier();
+          if (__builtin_amdgcn_readfirstlane(ia | ib) == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const int c = 4 * i + lg;
+              if (l16 >= c && l16 < w) {
+                st_dev(P + (int64_t)c * ld + l16, lf[i]);
+                if constexpr (IN32) st_dev(P32 + (int64_t)c * ld32 + l16, (float)lf[i]);
+              }
+              if (16 + l16 < w) {
+                st_dev(P + (int64_t)c * ld + 16 + l16, x[i]);
+                if constexpr (IN32) st_dev(P32 + (int64_t)c * ld32 + 16 + l16, (float)x[i]);
+                if (l16 >= c) {
+                  st_dev(P + (int64_t)(16 + c) * ld + 16 + l16, ld2[i]);
+                  if constexpr (IN32) st_dev(P32 + (int64_t)(16 + c) * ld32 + 16 + l16, (float)ld2[i]);
+                }
+              }
+            }
+            if (fwd && l16 < nrhs) {
+#pragma unroll
+              for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                  const int c = h * 16 + 4 * i + lg;
+                  if (c < w) st_dev(Bf + (int64_t)l16 * ldbf + c0 + c, y[h][0][i]);
+                }
+            }
+          }
+        } else {
+          lds_barrier();
+        }
+        const int info = __builtin_amdgcn_readfirstlane(s_pinfo);
+        if (info != 0) return info;
+      }
+      // the rows below the block (the panel is then 32 wide)
+      if (mine && (s0 > 0 || wave > 0)) {
+        double* const bp = fwd ? Bf + (int64_t)imin(lg, nrhs - 1) * ldbf + c0 + s0 : nullptr;
+        double b[2] = {0.0, 0.0};
+        if (fwd)
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb) b[rb] = bp[imin(rw + rb * 16 + l16, S - 1)];
+        d4 x1[2] = {acc[0][0], acc[1][0]}, x2[2] = {acc[0][1], acc[1][1]};
+        panel16_rows(x1, Fb, lane);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const double f = Xb[k * 64 + lane];
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb)
+            x2[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(f, x1[rb][k], x2[rb], 0, 0, 2 /* neg B */);
+        }
+        panel16_rows(x2, Fb + QUAD_OPS * 64, lane);
+        if (fwd) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const double y1 = Yb[k * 64 + lane], y2 = Yb[(4 + k) * 64 + lane];
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb) {
+              b[rb] = mfma4_f64_neg(y1, x1[rb][k], b[rb]);
+              b[rb] = mfma4_f64_neg(y2, x2[rb][k], b[rb]);
+            }
+          }
+        }
+        double* const q0 = P + (int64_t)lg * ld + s0 + rw + l16;
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+          if (rw + rb * 16 + l16 < S) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              st_dev(q0 + (int64_t)(4 * i) * ld + rb * 16, x1[rb][i]);
+              st_dev(q0 + (int64_t)(16 + 4 * i) * ld + rb * 16, x2[rb][i]);
+              if constexpr (IN32) {
+                float* const q32 = P32 + (int64_t)(4 * i + lg) * ld32 + s0 + rw + rb * 16 + l16;
+                st_dev(q32, (float)x1[rb][i]);
+                st_dev(q32 + 16 * ld32, (float)x2[rb][i]);
+              }
+            }
+            if (fwd && lg < nrhs) st_dev(bp + rw + rb * 16 + l16, b[rb]);
+          }
+      }
+      if (s0 + 128 < R) lds_barrier();  // the next slab's stages
+    }
+    // the panel must be visible to every wavefront before the next panel's
+    // update reads it
+    wait_vmcnt<0>();
+    lds_barrier();
   }
   return 0;
 }
@@ -2829,7 +3026,7 @@ __device__ __forceinline__ void prev_tile(const double* __restrict__ Lkk, const 
     for (int s0 = 16; s0 < R; s0 += 256) {
       gemm_core<128, 256, PW, 8, 4, 4, 0>(Bkk + (int64_t)c0 * ld + c0 + s0, Qkk + (int64_t)(c0 + 16) * ldq + c0 + s0,
                                           LTkk + (int64_t)(c0 + 16) * ldq + c0, ldq, imin(256, R - s0), w,
-                                          mpad - c0 - 16, false, lds, Ps + s0, PPLD, ld);
+                                          mpad - c0 - 16, lds, Ps + s0, PPLD, ld);
       __syncthreads();
     }
     {
@@ -3258,9 +3455,9 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
   // solves only, in half the LDS, two workgroups per compute unit; MODE 7 the
   // same with each system's matrix read from and L written to FP32 storage
   // (A32, the FP64 tile in A for the products and the solves)
-  static_assert(FRB_COMPACT_DOUBLES <= PT_LDS_COMPACT, "compact LDS budget");
+  static_assert(FRB_COMPACT_DOUBLES <= LDS_COMPACT_DOUBLES && PT_LDS_COMPACT <= LDS_COMPACT_DOUBLES, "compact LDS budget");
   constexpr bool COMPACT = MODE == 6 || MODE == 7;
-  __shared__ double lds[COMPACT ? PT_LDS_COMPACT : LDS_DOUBLES];
+  __shared__ double lds[COMPACT ? LDS_COMPACT_DOUBLES : LDS_DOUBLES];
   __shared__ int s_claim[5];
   __shared__ int32_t s_desc[DESC_WORDS];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -3446,7 +3643,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
       } else if (kind == TK_POTRF) {
         // up to PT_FWD right-hand sides: the forward solve rides along (its FTRSV task only passes the completion on)
         // MODE 7: the system's FP32 matrix at A32 + sr[5], leading dimension sr[7]
-        const int info = uniform_i(potrf_tile<SEG, 128, MODE == 7>(
+        const int info = uniform_i(potrf_slabs<MODE == 7>(
             Abase + (tk * nb) * ld + tk * nb, ld, tsz(tk), lds, fuse_fwd ? Bbase + tk * nb : nullptr, ldb,
             (int)a.nrhs, MODE == 7 ? a.A32 + sr[5] + (tk * nb) * sr[7] + tk * nb : nullptr, sr[7]));
         if (info != 0 && tid == 0)
