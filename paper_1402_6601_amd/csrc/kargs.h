@@ -10,6 +10,8 @@
 #define HDR_INFO 2     /* first failing pivot column (1-based), 0 if none   */
 #define HDR_ERROR 3    /* DEV_ERR_* code of the first runtime error, 0 if none */
 #define HDR_DONE 4     /* work items completed                              */
+#define HDR_FWD 5      /* the last FTRSV is done (single-matrix launches): L and the
+                          diagonal tiles' inverses are final                */
 #define HDR_WORDS 64   /* 256 bytes                                         */
 
 /* runtime error codes in HDR_ERROR */
@@ -50,6 +52,7 @@ typedef struct KArgs {
   int32_t inv_rows;     /* inv: rows of a TRSM item                               */
   int32_t finv;         /* inv: POTRF leaves L_kk^{-1} in Dinv (tiles of order <= 128),
                            and TRTRI, for the solve, writes DinvT only            */
+  int32_t lfinal;       /* a launch that only solves: L is final from the start    */
   double *Dinv;         /* mixed precision: L_kk^{-1}, nb x nb each (FP64); adjoint:
                            two scratch tiles per diagonal tile (Mn, Y^T)          */
   double *DinvT;        /* mixed precision, inv and adjoint: L_kk^{-T}, nb x nb each */

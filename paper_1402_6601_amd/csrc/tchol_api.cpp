@@ -343,6 +343,7 @@ int32_t execute(const Plan& plan, const Image& img, double* A, double* B, int64_
   a.inv = plan.inv ? 1 : 0;
   // POTRF leaves the inverses that the TRSMs apply where one workgroup factors a tile in LDS
   a.finv = plan.inv && plan.op != TCHOL_OP_SOLVE && plan.systems[0].nb <= 128 ? 1 : 0;
+  a.lfinal = plan.op == TCHOL_OP_SOLVE || plan.op == tchol::OP_SOLVE_INV || plan.op == tchol::OP_SOLVE_SUBST ? 1 : 0;
   a.H = H;
   a.hrows = hrows;
   a.A32 = A32;

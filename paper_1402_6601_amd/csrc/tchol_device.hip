@@ -2074,7 +2074,9 @@ __device__ __forceinline__ int potrf_slabs(double* __restrict__ Akk, int64_t ld,
 // of the step, to land during the solve.
 //
 // REV = 2: the same solve, also storing P^T at Qb (ld ldq): the explicit
-// inverse of the mixed-precision solve, from identity strips.
+// inverse, from identity strips.  rb0: the strip's columns before block rb0
+// are zero (an identity strip's before its own rows), so the steps over them
+// are left out.
 #define TS 32
 
 // Hs (non-null): the solved strip (its first row a multiple of 16 in the
@@ -2086,7 +2088,7 @@ template <typename TX, int REV = 0>
 __device__ __forceinline__ void trsm_strip(TX* __restrict__ X, int64_t ldx, const double* __restrict__ Lkk, int64_t ld,
                                            int S, int mk, double* lds, double* Qb = nullptr,
                                            int64_t ldq = 0, uint16_t* Hs = nullptr, int64_t hgs = 0,
-                                           int64_t hterm = 0) {
+                                           int64_t hterm = 0, int rb0 = 0) {
   double* Xs = lds;  // [2][512][16]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2198,8 +2200,8 @@ __device__ __forceinline__ void trsm_strip(TX* __restrict__ X, int64_t ldx, cons
     }
   };
   SolveData sa, sb;
-  if (wave < 2) fetch_solve(0, sa);
-  for (int rb = 0; rb < nblk; rb += 2) {
+  if (wave < 2) fetch_solve(rb0, sa);
+  for (int rb = rb0; rb < nblk; rb += 2) {
     step(rb, sa, sb);
     if (rb + 1 < nblk) step(rb + 1, sb, sa);
   }
@@ -2688,9 +2690,9 @@ __device__ __forceinline__ void tile_solve(const double* __restrict__ Lkk, int64
 // rows, a K range whose length is a multiple of 8 and starts even, even
 // leading dimensions and 16-byte aligned L and X; then every step of every
 // wavefront lies inside K and nothing is masked.
-template <typename TL, bool TRANS, bool ASSIGN>
-__device__ __forceinline__ void gemv_strip_wide(const TL* __restrict__ L, int64_t ld, double* Y, const double* X,
-                                                int64_t ldb, int k0, int k1, int nrhs, double* lds) {
+template <typename TL, bool TRANS, bool ASSIGN, class Late>
+__device__ __forceinline__ void gemv_strip_wide(const TL* L, int64_t ld, double* Y, const double* X,
+                                                int64_t ldb, int k0, int k1, int nrhs, double* lds, Late late) {
   typedef TL TL2 __attribute__((ext_vector_type(2)));
   typedef const __attribute__((address_space(1))) char gchar;
   typedef const __attribute__((address_space(1))) TL2 gTL2;
@@ -2725,6 +2727,7 @@ __device__ __forceinline__ void gemv_strip_wide(const TL* __restrict__ L, int64_
         fb[2 * j + 1] = (double)v1[1];
       }
     }
+  if (!late()) return;
   // output element (t, v) of a lane: strip row 2 (4 v + lg) + t (paired rows)
   // or 16 t + 4 v + lg (TRANS); this wavefront adds up two of the eight
   auto out_row = [&](int t, int v) __attribute__((always_inline)) {
@@ -2788,12 +2791,15 @@ __device__ __forceinline__ void gemv_strip_wide(const TL* __restrict__ L, int64_
 // trip per item.  The quarters' partial products meet in LDS and are added
 // in wavefront order, so the result does not depend on timing.  L in FP64
 // or FP32 (the mixed-precision working copy); X and Y in FP64.
-template <typename TL, bool TRANS, bool ASSIGN>
-__device__ __forceinline__ void gemv_strip(const TL* __restrict__ L, int64_t ld, double* Y, const double* X,
-                                           int64_t ldb, int rows, int k0, int k1, int nrhs, double* lds) {
+// late(), called by every wavefront once its fragments of L are requested,
+// waits for X and Y (an item claimed before its predecessors are done, on an L
+// that is final: its memory time then passes during the wait); false: give up.
+template <typename TL, bool TRANS, bool ASSIGN, class Late>
+__device__ __forceinline__ void gemv_strip(const TL* L, int64_t ld, double* Y, const double* X,
+                                           int64_t ldb, int rows, int k0, int k1, int nrhs, double* lds, Late late) {
   if (rows == 32 && ((k1 - k0) & 7) == 0 && (k0 & 1) == 0 && ((ld | ldb) & 1) == 0 &&
       ((reinterpret_cast<uintptr_t>(L) | reinterpret_cast<uintptr_t>(X)) & 15) == 0) {
-    gemv_strip_wide<TL, TRANS, ASSIGN>(L, ld, Y, X, ldb, k0, k1, nrhs, lds);
+    gemv_strip_wide<TL, TRANS, ASSIGN>(L, ld, Y, X, ldb, k0, k1, nrhs, lds, late);
     return;
   }
   double* Ps = lds;  // [wavefront][8][64]: the partial products
@@ -2829,6 +2835,7 @@ __device__ __forceinline__ void gemv_strip(const TL* __restrict__ L, int64_t ld,
         fb[u] = (double)*(gTL*)(Lu + (offb + oc));
       }
     }
+  if (!late()) return;
   // this wavefront's two outputs of the strip's eight per lane: block wave / 2,
   // rows 4 v + lg with v = 2 (wave % 2) + h
   const int ob = wave >> 1;
@@ -3295,21 +3302,28 @@ __device__ __forceinline__ int uniform_i(int v) { return __builtin_amdgcn_readfi
 // task's counter reaches zero; false when the run is being aborted or the
 // wait exceeded its bound.
 // one (not null): a single-matrix launch's failure word, read along with the
-// first look (and again after a wait) into failed.
-__device__ __forceinline__ bool wait_ready(const KArgs& a, int task, int lane, const int32_t* one, int& failed) {
+// first look (and again after a wait) into failed.  early(), asked when the
+// first look finds the task not ready: true to go on without waiting (the work
+// item then waits itself).
+template <class Early>
+__device__ __forceinline__ bool wait_ready(const KArgs& a, int task, int lane, const int32_t* one, int& failed,
+                                           Early early) {
   const int dep0 = ld_relaxed(&a.dep[task]), abort0 = ld_relaxed(&a.hdr[HDR_ABORT]);  // all in flight at once
   const int f0 = one ? ld_relaxed(one) : 0;
   failed = uniform_i(f0);
   if (uniform_i(dep0) == 0) return uniform_i(abort0) == 0;
+  if (uniform_i(abort0) == 0 && early()) return true;
   const uint64_t t0 = wall_clock64();
-  for (;;) {
+  for (int poll = 0;; ++poll) {
     __builtin_amdgcn_s_sleep(2);
-    // the counter and the abort flag in flight together: one round trip per poll
+    // the counter and the failure word in flight together: one round trip per
+    // poll; the abort flag, in a line that every waiting worker would read and
+    // the tickets are drawn from, on every eighth (a task that is ready may run)
     const int d = ld_relaxed(&a.dep[task]), f = one ? ld_relaxed(one) : 0;
-    const int ab = uniform_i(ld_relaxed(&a.hdr[HDR_ABORT]));
     failed = uniform_i(f);
-    if (uniform_i(d) == 0) return ab == 0;
-    if (ab != 0) return false;
+    if (uniform_i(d) == 0) return true;
+    if ((poll & 7) != 7) continue;
+    if (uniform_i(ld_relaxed(&a.hdr[HDR_ABORT])) != 0) return false;
     if ((int64_t)(wall_clock64() - t0) > a.wait_limit) {
       if (lane == 0) {
         __hip_atomic_store(&a.hdr[HDR_ERROR], DEV_ERR_TIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -3353,6 +3367,7 @@ __device__ __forceinline__ void raise_error(const KArgs& a, int code) {
 #define PL_P 2         // + b: P(b) done
 #define PL_S 8         // + 4 r + b: strips of S(r, b) done
 #define PL_U 24        // + 4 r + c: updates applied to sub-block (r, c)
+#define PL_INV 44      // items of the tile's TRTRI done
 
 struct PoolUnit {
   int type, b, r, c, s;  // type 0: P(b); 1: S(r, b, s); 2: U(r, c, b); -1: none left
@@ -3458,13 +3473,14 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
   static_assert(FRB_COMPACT_DOUBLES <= LDS_COMPACT_DOUBLES && PT_LDS_COMPACT <= LDS_COMPACT_DOUBLES, "compact LDS budget");
   constexpr bool COMPACT = MODE == 6 || MODE == 7;
   __shared__ double lds[COMPACT ? LDS_COMPACT_DOUBLES : LDS_DOUBLES];
-  __shared__ int s_claim[5];
+  __shared__ int s_claim[6];
   __shared__ int32_t s_desc[DESC_WORDS];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = uniform_i(tid >> 6);
   // wavefront 0's record of the work item it ran last, published at the
   // start of the next claim, and of the items this worker completed
   int p_task = -1, p_ticket = 0, p_parts = 0, p_e0 = 0, p_e1 = 0, ndone = 0;
+  bool p_fwd = false;  // it was an item of the last FTRSV
   uint64_t p_end = 0;
   // wavefront 0: the POTRF pool this worker serves (pl_task < 0: none) and
   // the POTRF work item's record, published when the pool has run dry
@@ -3483,7 +3499,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
     // its descriptor is fetched.  A worker in a POTRF pool takes the pool's
     // next sub-unit instead, and returns to the tickets when none is left.
     if (wave == 0) {
-      int task = -1, part = 0, unit = -1, t = 0, failed = 0;
+      int task = -1, part = 0, unit = -1, t = 0, failed = 0, early = 0;
       bool claimed = false;
       uint64_t tw = 0;
       if (POOLED && pl_task >= 0) {
@@ -3517,9 +3533,12 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         }
         if (p_task >= 0) {
           // the last work item of a task activates its successors
-          if (uniform_i(prev) == p_parts - 1)
+          if (uniform_i(prev) == p_parts - 1) {
             for (int e = p_e0 + lane; e < p_e1; e += 64)
               __hip_atomic_fetch_sub(&a.dep[a.succ[e]], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (SOLVE_KINDS && p_fwd && lane == 0)
+              __hip_atomic_store(&a.hdr[HDR_FWD], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
           ++ndone;
           if (a.trace && lane == 0) {
             a.trace[4 * (int64_t)p_ticket + 2] = p_end;
@@ -3533,7 +3552,37 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
           part = uniform_i(a.items[2 * t + 1]);
           if (a.trace) tw = wall_clock64();
           const int dv = lane < DESC_WORDS ? a.desc[DESC_WORDS * (int64_t)task + lane] : 0;
-          if (!wait_ready(a, task, lane, one_failed, failed)) task = -1;
+          // A strip of the solve whose L (or inverse) is already final starts
+          // before its right-hand sides are: it requests L, then waits.  L is
+          // final from the start in a launch that only solves, and everywhere once
+          // the last FTRSV is done (HDR_FWD); a diagonal tile's inverse once
+          // its TRTRI items have counted up its pool word.  Not at tiles of at
+          // most 128, whose strips read too little for it (n = 300 at 64: 266 us
+          // without, 275 with; n = 16384 at 512, solve alone: 2.50 ms without, 1.84 with).
+          auto early_ok = [&]() __attribute__((always_inline)) {
+            if constexpr (!SOLVE_KINDS || MODE == 4) return false;
+            if (!one_matrix || s_sys[SYS_WORDS * uniform_i(__builtin_amdgcn_readlane(dv, 7)) + 3] <= PSB) return false;
+            const int kd = uniform_i(__builtin_amdgcn_readlane(dv, 0)), pd = uniform_i(__builtin_amdgcn_readlane(dv, 4));
+            bool ok = false;
+            if (kd == TK_FGEMV) {
+              ok = a.lfinal != 0;
+            } else if (kd == TK_BGEMV) {
+              ok = a.lfinal != 0 || uniform_i(ld_relaxed(&a.hdr[HDR_FWD])) != 0;
+            } else if ((kd == TK_FTRSV || kd == TK_BTRSV) && pd > 1) {  // by strips, with the tile's inverse
+              if (MODE == 2) {
+                ok = true;
+              } else {
+                const int tkd = uniform_i(__builtin_amdgcn_readlane(dv, 3)), sd = uniform_i(__builtin_amdgcn_readlane(dv, 7));
+                const int64_t* srd = s_sys + SYS_WORDS * sd;
+                const int m = (int)tile_size(srd[2], srd[3], tkd);
+                ok = uniform_i(ld_relaxed(a.pool + POOL_WORDS * (srd[6] + tkd) + PL_INV)) ==
+                     uniform_i((m + a.trsm_rows - 1) / a.trsm_rows);
+              }
+            }
+            early = ok ? 1 : 0;
+            return ok;
+          };
+          if (!wait_ready(a, task, lane, one_failed, failed, early_ok)) task = -1;
           if (lane < DESC_WORDS) s_desc[lane] = dv;
           const int kd = uniform_i(__builtin_amdgcn_readlane(dv, 0)), pd = uniform_i(__builtin_amdgcn_readlane(dv, 4));
           if (POOLED && task >= 0 && kd == TK_POTRF && pd > 1) {
@@ -3568,6 +3617,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         s_claim[2] = t;
         s_claim[3] = unit;
         s_claim[4] = failed;
+        s_claim[5] = early;
         if (a.trace && task >= 0 && !claimed) {
           a.trace[4 * (int64_t)t + 0] = tw;
           a.trace[4 * (int64_t)t + 1] = wall_clock64();
@@ -3617,6 +3667,25 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
     // its remaining tasks on, so that the DAG drains
     const bool skip = one_matrix ? uniform_i(s_claim[4]) != 0 : a.batched && uniform_i(ld_relaxed(&a.sinfo[sid])) != 0;
     int ok = 1;
+    // the wait of a strip that was claimed early (all wavefronts): false when the run is being aborted
+    const bool was_early = uniform_i(s_claim[5]) != 0;
+    auto late = [&]() __attribute__((always_inline)) {
+      if (!was_early) return true;
+      if (wave == 0) {
+        int f;
+        const bool go = wait_ready(a, task, lane, nullptr, f, []() __attribute__((always_inline)) { return false; });
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if (lane == 0) {
+          s_claim[5] = go;
+          if (a.trace) a.trace[4 * (int64_t)ticket + 1] = wall_clock64();
+        }
+      }
+      lds_barrier();
+      const bool go = uniform_i(s_claim[5]) != 0;
+      if (!go) ok = 0;
+      return go;
+    };
+    int count_inv = 0;  // a TRTRI item of an FP64 launch counts up its tile's pool word
     // A unit of a POTRF pool runs the POTRF, TRSM or GEMM body on sub-blocks
     // of the diagonal tile (tk, tk): po_* give the sub-block offsets (rows,
     // columns, panel columns) and sizes; whole tasks take the tile's.
@@ -3698,7 +3767,10 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         }
         if (info != 0 && tid == 0) {
           if (a.batched) {
-            __hip_atomic_store(&a.sinfo[sid], (int)(tk * nb) + info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // (the first failure stays: a later tile may be reached before it is seen there)
+            int none = 0;
+            __hip_atomic_compare_exchange_strong(&a.sinfo[sid], &none, (int)(tk * nb) + info, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           } else {
             __hip_atomic_store(&a.hdr[HDR_INFO], (int)(tk * nb) + info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(&a.hdr[HDR_ABORT], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -3853,13 +3925,13 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
           if (kind == TK_FTRSV && MODE == 0)  // L_kk^{-1} = (L_kk^{-T})^T: rows of it are columns of DinvT
             gemv_strip<double, true, true>(DinvTSys + (int64_t)tk * nb * nb + (int64_t)r0 * nb, nb,
                                            Sbase + tk * nb + r0, Bbase + tk * nb, ldb, rows, 0, imin(m, r0 + rows),
-                                           (int)a.nrhs, lds);
+                                           (int)a.nrhs, lds, late);
           else if (kind == TK_FTRSV)
             gemv_strip<double, false, true>(DinvSys + (int64_t)tk * nb * nb + r0, nb, Sbase + tk * nb + r0,
-                                            Bbase + tk * nb, ldb, rows, 0, imin(m, r0 + rows), (int)a.nrhs, lds);
+                                            Bbase + tk * nb, ldb, rows, 0, imin(m, r0 + rows), (int)a.nrhs, lds, late);
           else
             gemv_strip<double, false, true>(DinvTSys + (int64_t)tk * nb * nb + r0, nb, Bbase + tk * nb + r0,
-                                            Sbase + tk * nb, ldb, rows, r0, m, (int)a.nrhs, lds);
+                                            Sbase + tk * nb, ldb, rows, r0, m, (int)a.nrhs, lds, late);
         } else if constexpr (MODE == 0) {
           // substitution against L_kk, in place (batched systems; an order not a multiple of 16)
           tile_solve(Abase + (tk * nb) * ld + tk * nb, ld, Bbase + tk * nb, ldb, tsz(tk), (int)a.nrhs,
@@ -3878,7 +3950,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         // y_k is in the scratch vector when the diagonal step applied an inverse
         const double* Yk = inv_tile(tk) ? a.S + sr[1] + tk * nb : Bbase + tk * nb;
         gemv_strip<E, false, false>(Abase + (tk * nb) * ld + ti * nb + r0, ld, Bbase + ti * nb + r0, Yk, ldb, rows,
-                                    0, tsz(tk), (int)a.nrhs, lds);
+                                    0, tsz(tk), (int)a.nrhs, lds, late);
         break;
       }
       case TK_BGEMV: {
@@ -3890,7 +3962,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         const int cols = imin(a.gemv_rows, tsz(ti) - c0);
         double* Yi = inv_tile(ti) ? a.S + sr[1] + ti * nb + c0 : Bbase + ti * nb + c0;
         gemv_strip<E, true, false>(Abase + (ti * nb + c0) * ld + tk * nb, ld, Yi, Bbase + tk * nb, ldb, cols, 0,
-                                   tsz(tk), (int)a.nrhs, lds);
+                                   tsz(tk), (int)a.nrhs, lds, late);
         break;
       }
       case TK_TRTRI: {
@@ -3915,12 +3987,15 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
           __syncthreads();
           if constexpr (MODE == 0)  // with L_kk^{-1} too (Dinv), if the TRSM items apply it (and not POTRF(k)'s)
             trsm_strip<double, 2>(X, nb, Abase + (tk * nb) * ld + tk * nb, ld, S, mpad, lds,
-                                  a.finv ? nullptr : DinvSys + (int64_t)tk * nb * nb + (int64_t)r0 * nb, nb);
+                                  a.finv ? nullptr : DinvSys + (int64_t)tk * nb * nb + (int64_t)r0 * nb, nb, nullptr, 0,
+                                  0, r0 >> 4);
           else if constexpr (MODE == 3)  // the adjoint: L (its A) is the factor
-            trsm_strip<double>(X, nb, Abase + (tk * nb) * ld + tk * nb, ld, S, mpad, lds);
+            trsm_strip<double>(X, nb, Abase + (tk * nb) * ld + tk * nb, ld, S, mpad, lds, nullptr, 0, nullptr, 0, 0,
+                               r0 >> 4);
           else
             trsm_strip<double, 2>(X, nb, Dsys + (int64_t)tk * nb * nb, nb, S, mpad, lds,
-                                  DinvSys + (int64_t)tk * nb * nb + (int64_t)r0 * nb, nb);
+                                  DinvSys + (int64_t)tk * nb * nb + (int64_t)r0 * nb, nb, nullptr, 0, 0, r0 >> 4);
+          count_inv = MODE == 0 ? 1 : 0;
         }
         break;
       }
@@ -4043,6 +4118,9 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
                                __HIP_MEMORY_SCOPE_AGENT);
       }
     } else if (wave == 0) {
+      if (count_inv && lane == 0)
+        __hip_atomic_fetch_add(a.pool + POOL_WORDS * (sr[6] + tk) + PL_INV, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      p_fwd = kind == TK_FTRSV && (int64_t)(tk + 1) * nb >= sn;
       p_task = ok ? task : -1;
       p_ticket = ticket;
       p_parts = d_parts;
