@@ -112,6 +112,7 @@ int64_t weight(int32_t kind, int32_t op) {
     case TK_SYRK: return 4;
     case TK_GEMM: return 6;
     case TK_GEMM2: return 12;
+    case TK_GEMM4: return 24;
     case TK_FTRSV: case TK_BTRSV: return 1;
     case TK_GREV: return 6;
     case TK_TREV: return 3;
@@ -137,7 +138,8 @@ int64_t run_weight(const Plan& p, int64_t t) {
     case TK_TRSM: return p.finv ? 10 + 8 * nb / 128 : 5 + 25 * nb / 128;
     case TK_SYRK: return 7 + 6 * nb / 128;
     case TK_GEMM: return 7 + 6 * nb / 128;
-    case TK_GEMM2: return 12 + 32 * nb / 128;
+    case TK_GEMM2: return 12 + 27 * nb / 128;
+    case TK_GEMM4: return 12 + 58 * nb / 128;
     case TK_TRTRI: return 5 + 34 * nb / 128;
     case TK_FTRSV: case TK_BTRSV: return p.inv ? 6 + 2 * nb / 128 : 8 + 25 * nb / 128;
     default: return 6 + 2 * nb / 128;
@@ -179,8 +181,17 @@ void build_factor(Builder& b, FactorIds* ids = nullptr, bool trtri = false, bool
   // order); the last update before TRSM(i, j) stays a single GEMM, so the
   // critical path does not wait for a double update.  id_gemm[(i, j, k)]
   // holds the task that applies update k (a GEMM2 under both of its k).
-  auto pair_first = [](int32_t j, int32_t k) { return (k % 2 == 0) && (k + 1 <= j - 2); };
-  auto pair_second = [](int32_t j, int32_t k) { return (k % 2 == 1) && (k <= j - 2); };
+  // Run plans merge aligned quadruples (k .. k+3, k % 4 == 0, k+3 <= j-2) the
+  // same way (GEMM4), and pairs where no quadruple fits.
+  const bool quads = b.p.quads;
+  auto group_last = [quads](int32_t j, int32_t k) {  // the last update of the task that applies update k
+    if (quads && (k & ~3) + 3 <= j - 2) return (k & ~3) + 3;
+    return (k & ~1) + 1 <= j - 2 ? (k & ~1) + 1 : k;
+  };
+  auto group_first = [quads](int32_t j, int32_t k) {
+    if (quads && (k & ~3) + 3 <= j - 2) return k & ~3;
+    return (k & ~1) + 1 <= j - 2 ? k & ~1 : k;
+  };
   auto gemm_parts = [&](int32_t i, int32_t j) {
     return Builder::cdiv(b.tile_size(i), b.s.gemm_m) * Builder::cdiv(b.tile_size(j), b.s.gemm_n);
   };
@@ -202,13 +213,12 @@ void build_factor(Builder& b, FactorIds* ids = nullptr, bool trtri = false, bool
       int32_t sb = Builder::cdiv(b.tile_size(i), b.s.syrk_b);
       id_syrk[ix2(i, k)] = b.add(TK_SYRK, i, i, k, sb * (sb + 1) / 2);
       for (int32_t j = k + 1; j < i; ++j) {
-        if (pair_first(j, k)) continue;  // created with its second update, after TRSM(., k+1)
-        const bool second = pair_second(j, k);
-        const int32_t id = second ? b.add(TK_GEMM2, i, j, k - 1, gemm_parts(i, j))
-                                  : b.add(TK_GEMM, i, j, k, Builder::cdiv(b.tile_size(i), b.s.gemm1_m) *
-                                                                Builder::cdiv(b.tile_size(j), b.s.gemm1_n));
-        id_gemm[ix3(i, j, k)] = id;
-        if (second) id_gemm[ix3(i, j, k - 1)] = id;
+        if (group_last(j, k) != k) continue;  // created with its last update, after TRSM(., k)
+        const int32_t k0 = group_first(j, k), len = k - k0 + 1;
+        const int32_t id = len > 1 ? b.add(len == 4 ? TK_GEMM4 : TK_GEMM2, i, j, k0, gemm_parts(i, j))
+                                   : b.add(TK_GEMM, i, j, k, Builder::cdiv(b.tile_size(i), b.s.gemm1_m) *
+                                                                 Builder::cdiv(b.tile_size(j), b.s.gemm1_n));
+        for (int32_t q = k0; q <= k; ++q) id_gemm[ix3(i, j, q)] = id;
       }
     }
   }
@@ -227,7 +237,7 @@ void build_factor(Builder& b, FactorIds* ids = nullptr, bool trtri = false, bool
       succ[id_syrk[ix2(i, k)]].push_back(k + 1 < i ? id_syrk[ix2(i, k + 1)] : id_potrf[i]);
       // each update task passes the tile on to the next one, the last to TRSM(i, j)
       for (int32_t j = k + 1; j < i; ++j) {
-        if (pair_first(j, k)) continue;
+        if (group_last(j, k) != k) continue;
         succ[id_gemm[ix3(i, j, k)]].push_back(k + 1 < j ? id_gemm[ix3(i, j, k + 1)] : id_trsm[ix2(i, j)]);
       }
     }
@@ -438,8 +448,8 @@ std::tuple<int32_t, int32_t, int32_t, int32_t, int32_t> tie_key(const Plan& p, i
   const bool adjoint = p.op == TCHOL_OP_BACKWARD;
   if (adjoint) step = T - 1 - p.tk[t];  // the adjoint runs its steps downwards
   int32_t kord = kind;
-  if (kind == TK_GEMM2) {  // a double update belongs to the step of its second update
-    step = p.tk[t] + 1;
+  if (kind == TK_GEMM2 || kind == TK_GEMM4) {  // a merged update belongs to the step of its last update
+    step = p.tk[t] + (kind == TK_GEMM2 ? 1 : 3);
     kord = TK_GEMM;
   }
   // the inverses that the factorization's TRSMs apply: right after POTRF(k)
@@ -645,7 +655,7 @@ bool finalize(Plan& p, std::vector<std::vector<int32_t>>& succ, int32_t policy, 
 }  // namespace
 
 std::shared_ptr<Plan> build_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed,
-                                 const Split& split, bool run) {
+                                 const Split& split, bool run, bool quads) {
   auto plan = std::make_shared<Plan>();
   Plan& p = *plan;
   p.op = op;
@@ -654,6 +664,7 @@ std::shared_ptr<Plan> build_plan(int32_t op, int64_t n, int64_t nb, int32_t poli
   p.policy = policy;
   p.seed = seed;
   p.run = run;
+  p.quads = quads;
   p.finv = run && op == OP_FACTOR_INVT;
   int64_t T64 = n == 0 ? 0 : (n + nb - 1) / nb;
   // the factorization's DAG has about T^3/6 tasks, the adjoint's T^3/3
@@ -694,9 +705,10 @@ std::shared_ptr<Plan> build_plan(int32_t op, int64_t n, int64_t nb, int32_t poli
 }
 
 std::shared_ptr<Plan> build_batched_plan(const std::vector<System>& systems, int32_t policy, uint32_t seed,
-                                         const Split& split, bool inv) {
+                                         const Split& split, bool inv, bool quads) {
   auto plan = std::make_shared<Plan>();
   Plan& p = *plan;
+  p.quads = quads;
   p.op = TCHOL_OP_BATCHED;
   p.inv = inv && systems.size() == 1;
   p.policy = policy;
@@ -822,9 +834,8 @@ std::shared_ptr<const Plan> cached_run_plan(int32_t op, int64_t n, int64_t nb, i
 std::shared_ptr<const Plan> get_run_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed) {
   if (op != TCHOL_OP_FACTOR && op != OP_FACTOR_INVT) return get_plan(op, n, nb, policy, seed);
   const int64_t rt = run_tile(n, nb);
-  if (rt > kRunTile) return get_plan(op, n, nb, policy, seed);
   return cached_run_plan(op, n, rt, policy, seed, [&]() -> std::shared_ptr<const Plan> {
-    return build_plan(op, n, rt, policy, seed, run_split(op, rt), true);
+    return build_plan(op, n, rt, policy, seed, run_split(op, rt), rt <= kRunTile, true);
   });
 }
 
@@ -834,7 +845,10 @@ std::shared_ptr<const Plan> get_run_merged_plan(int64_t n, int64_t nb, int32_t p
   systems[0].n = n;
   systems[0].nb = rt;
   systems[0].ld = n;
-  if (rt > kRunTile) return get_batched_plan(systems, policy, seed, inv);
+  if (rt > kRunTile)
+    return cached_run_plan(inv ? OP_FACTOR_INVT : TCHOL_OP_FACTOR, n, nb, policy, seed, [&]() -> std::shared_ptr<const Plan> {
+      return build_batched_plan(systems, policy, seed, default_split(), inv, true);
+    });
   // the key's operation: with and without inverses
   return cached_run_plan(inv ? OP_FACTOR_INVT : TCHOL_OP_FACTOR, n, nb, policy, seed, [&]() -> std::shared_ptr<const Plan> {
     if ((n + rt - 1) / rt > 1200) return nullptr;
@@ -843,7 +857,7 @@ std::shared_ptr<const Plan> get_run_merged_plan(int64_t n, int64_t nb, int32_t p
     p.op = TCHOL_OP_BATCHED;
     p.n = n;
     p.nb = rt;
-    p.run = true;
+    p.run = p.quads = true;
     p.inv = p.finv = inv;
     p.policy = policy;
     p.seed = seed;

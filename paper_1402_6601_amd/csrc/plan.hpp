@@ -50,6 +50,7 @@ struct Plan {
   uint32_t seed = 0;       // for TCHOL_POLICY_RANDOM
   std::vector<System> systems;             // one for factor and solve plans
   Split split;             // the work items' sizes
+  bool quads = false;      // a run plan: four updates of a tile merged where two are else
   bool run = false;        // a run plan by tiles of at most 128 (its work items cost run_weight)
   bool finv = false;       // POTRF leaves L_kk^{-1} for the TRSMs (run plans by tiles of at most 128)
   bool inv = false;        // the FP64 solve in it applies explicit inverses of the diagonal
@@ -89,7 +90,7 @@ std::shared_ptr<const Plan> get_plan(int32_t op, int64_t n, int64_t nb, int32_t 
 
 // Uncached build, used by get_plan and by the plan-introspection entry point.
 std::shared_ptr<Plan> build_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed,
-                                 const Split& split, bool run = false);
+                                 const Split& split, bool run = false, bool quads = false);
 
 // Factorization followed by the solve, for every system, as one DAG: each
 // system's factor tasks, then its solve tasks, joined by the data-flow
@@ -100,7 +101,7 @@ std::shared_ptr<Plan> build_plan(int32_t op, int64_t n, int64_t nb, int32_t poli
 // a multiple of 16).  Uncached.  Returns nullptr if the task count exceeds
 // what the kernel indexes.
 std::shared_ptr<Plan> build_batched_plan(const std::vector<System>& systems, int32_t policy, uint32_t seed,
-                                         const Split& split, bool inv = false);
+                                         const Split& split, bool inv = false, bool quads = false);
 
 // The batched plan for these systems' orders and tile sizes, from a small
 // process-wide cache keyed by them (offsets and leading dimensions are not
@@ -113,8 +114,9 @@ std::shared_ptr<const Plan> get_batched_plan(const std::vector<System>& systems,
 int64_t run_tile(int64_t n, int64_t nb);
 
 // The plans launches run: as get_plan and the merged get_batched_plan, with
-// the factorization at tiles of run_tile(n, nb) and, there, the finer work
-// items of run_split.  The merged plan's solve keeps the caller's tiles: its
+// four updates of a tile merged into one task where they allow, the
+// factorization at tiles of run_tile(n, nb) and, at tiles of at most 128, the
+// finer work items of run_split.  The merged plan's solve keeps the caller's tiles: its
 // systems are the matrix at run_tile (factor tasks) and at nb (solve tasks).
 std::shared_ptr<const Plan> get_run_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed);
 // inv as for build_batched_plan.

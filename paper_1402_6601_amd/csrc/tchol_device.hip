@@ -3825,7 +3825,8 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
       }
       case TK_SYRK:
       case TK_GEMM:
-      case TK_GEMM2: {
+      case TK_GEMM2:
+      case TK_GEMM4: {
         if constexpr (!FACTOR_KINDS) {
           ok = 0;
           break;
@@ -3846,9 +3847,9 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         }
         int M = imin(bm, tsz(ti) - si * bm);
         int N = imin(bn, tsz(tj) - sj * bn);
-        // a double update streams the panel columns of steps k and k + 1,
-        // which are adjacent in the matrix: one product with K = 2 nb
-        int K = kind == TK_GEMM2 ? tsz(tk) + tsz(tk + 1) : tsz(tk);
+        // a merged update streams the panel columns of its two or four steps,
+        // which are adjacent in the matrix: one product with K = 2 nb or 4 nb
+        int K = tsz(tk) * (kind == TK_GEMM2 ? 2 : kind == TK_GEMM4 ? 4 : 1);
         bool lower = kind == TK_SYRK && si == sj;
         int64_t crow = (int64_t)ti * nb + si * bm, ccol = (int64_t)tj * nb + sj * bn, kcol = (int64_t)tk * nb;
         int64_t brow = (int64_t)tj * nb + sj * bn;

@@ -32,6 +32,8 @@
 #define TK_PADJS 17  /* Q_kk = L_kk^{-T} Y_k + Y_k^T L_kk^{-1}, Lbar_kk = tril(Q_kk)/2 */
 /* adjoint: two consecutive links of a GREV chain in one task (K = 2 nb) */
 #define TK_GREV2 18  /* Lbar_ik <- Lbar_ik - Q_ij L_jk - Q_i,j+1 L_j+1,k        */
-#define TK_NKINDS 19
+/* factorization, run plans: four consecutive updates of one tile in one task (K = 4 nb) */
+#define TK_GEMM4 19  /* A_ij <- A_ij - sum of L_iq L_jq^T, q = k .. k+3        */
+#define TK_NKINDS 20
 #define TCHOL_PRB 64  /* block order of the TK_PADJ* products                      */
 #endif
