@@ -786,10 +786,14 @@ std::shared_ptr<const Plan> get_batched_plan(const std::vector<System>& systems,
 // The critical path of a factorization by tiles of nb is T steps of POTRF,
 // inverse, TRSM and SYRK, each a chain of dependent work items whose length
 // grows with nb, against n^3 / 3 flops shared by all workgroups.  Tiles of 128
-// have by far the shortest path (POTRF with the inverse 29 us, TRSM 6 us, SYRK
-// 7 us per 128 columns, where a 512 tile takes 790 us for its four times as
-// many), but their updates, of 128 or 256 columns, pay the work items' fixed
-// cost (load and store of the output tile) four times as often.
+// have by far the shortest path (POTRF with the inverse 31-33 us, TRSM 14-17
+// us, SYRK 10-11 us and 8 us between them per 128 columns, where a 512 tile
+// takes 790 us for its four times as many), but their updates, of 128 to 512
+// columns, pay the work items' fixed cost (load and store of the output tile)
+// more often.  Factor and solve of 16 right-hand sides, caller's nb = 512, at
+// tiles of 128 / 256 / 512: n = 8192 5.6 / 9.1 / 10.8 ms, 12288 14.7 / 15.7 /
+// 17.0, 14336 22.1 / 22.2 / 21.0, 16384 31.6 / 30.2 / 28.2: the line lies below
+// the last two, and 256 is never the best.
 constexpr int64_t kRunTile = 128;
 constexpr int64_t kRunTileOrder = 12288;
 

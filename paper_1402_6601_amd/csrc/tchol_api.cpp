@@ -581,8 +581,8 @@ int64_t factor_solve_bytes(int64_t n, int64_t nb, int64_t nrhs, bool inv) {
 }
 
 // The same for the plan that the launch runs when its workspace holds it.
-int64_t factor_solve_run_bytes(int64_t n, int64_t nb, int64_t nrhs, bool inv) {
-  auto plan = tchol::get_run_merged_plan(n, nb, TCHOL_POLICY_LIST, 0, inv);
+int64_t factor_solve_run_bytes(int64_t n, int64_t nb, int64_t nrhs) {
+  auto plan = tchol::get_run_merged_plan(n, nb, TCHOL_POLICY_LIST, 0, true);
   return plan ? inv_layout(*plan, nrhs).end : 0;
 }
 
@@ -743,7 +743,8 @@ int64_t tchol_factor_solve_workspace_bytes(int64_t n, int64_t nb, int64_t nrhs) 
   if (nrhs < 0) return -3;
   const int64_t need = tchol::factor_solve_bytes(n, nb, nrhs, true);
   if (need < 0) return need;
-  return std::max({need, tchol::factor_solve_run_bytes(n, nb, nrhs, true), tchol::factor_solve_run_bytes(n, nb, nrhs, false)});
+  // the inverses (n nb doubles) make the substituting launch's plans the smaller ones
+  return std::max(need, tchol::factor_solve_run_bytes(n, nb, nrhs));
 }
 
 int32_t tchol_factor_solve(double* A, int64_t n, int64_t nb, double* B, int64_t nrhs, void* ws, int64_t ws_bytes,

@@ -75,9 +75,6 @@ __device__ __forceinline__ uint32_t lds_addr(double* l) {
 __device__ __forceinline__ void dma16(const void* g, double* l) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr(l)), "v"(g) : "memory");
 }
-__device__ __forceinline__ void dma4(const void* g, double* l) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" : : "s"(lds_addr(l)), "v"(g) : "memory");
-}
 // The same from a wave-uniform base (scalar registers) plus a per-lane byte
 // offset below 4 GB: one 32-bit register per lane instead of a 64-bit address.
 __device__ __forceinline__ const void* uniform_ptr(const void* p) {
@@ -183,19 +180,21 @@ __device__ __forceinline__ void wait_vmcnt() {
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
 
 // ---------------------------------------------------------------------------
-// Matrix-core tile product used by every update:
-//     C[M x N] -= Ap[M x K] * Bp[N x K]^T,   M <= BM, N <= BN, K % KC == 0.
+// Matrix-core tile product for a result that stays in LDS (the panels of
+// potrf_tile and prev_tile, the adjoint's 64 x 64 blocks; whole work items of
+// 128 x 128 take gemm_tile, below):
+//     C[M x N] - Ap[M x K] * Bp[N x K]^T,   M <= BM, N <= BN, K % KC == 0.
 // The four wavefronts form a WGM x (4/WGM) grid; each owns a (BM/WGM) x
 // (BN*WGM/4) piece of C as 16x16 MFMA blocks held in registers from the load
-// of C to the final store.  K is streamed in chunks of KC
+// of C to the end.  K is streamed in chunks of KC
 // columns through NST LDS stages filled by direct-to-LDS loads, NST-1 chunks
 // ahead of the matrix cores.  SEG = 128 moves 16 bytes per lane (rows in
 // pairs) and needs even ld, 16-byte aligned panels, and, when M or N is odd,
 // one readable row after the panel; SEG = 32 moves 4 bytes per lane and has
 // no such needs.  Row indices are clamped into the panel
-// (rows past M hold copies and only feed outputs that are never stored).  With lower_only, entries of C above its diagonal are untouched.
-// With Cl set, the result goes to LDS at Cl (column-major, leading dimension
-// ldl; it must not overlap the NST stages) instead of back to C.
+// (rows past M hold copies and only feed outputs that are never used).
+// gemm_core's result goes to LDS at Cl (column-major, leading dimension ldl;
+// it must not overlap the NST stages).
 //
 // The chunk loop is kept free of branches in its steady state (the transfer
 // width is fixed per kernel instance, a transfer slot's panel is known at
@@ -1367,9 +1366,11 @@ __device__ __forceinline__ void panel16_rows(d4 (&x)[NX], const double* Fb, int 
 // (ldi), zeros above its diagonal included; rows and columns from m to the
 // next multiple of 16 are the identity's.
 //
-// Bound by the chain: per panel about 2900 cycles of panel16 (vector
-// instructions issue every 5 to 8 cycles for one wavefront) and 900 of the
-// two products, two barriers and their LDS round trips.
+// Bound by the chain: per panel about 2800 cycles of panel16 (vector
+// instructions issue every 5 to 8 cycles for one wavefront) and 1400 of the
+// two products, two barriers and their LDS round trips.  A tile of 128 in a
+// factorization of order 1024: 62.7 us, and 31 more for the inverse by TRTRI
+// strips, became 31-33 us with the inverse.
 // Returns 0, or the 1-based column (within the tile) whose pivot is not
 // positive (the columns before its panel's are then stored).
 #define SLD 144   // LDS leading dimension of the resident tile (fragment rows 128 bytes apart modulo 256: no conflicts)
@@ -2266,7 +2267,8 @@ __device__ __forceinline__ void trsm_inv_rows(double* __restrict__ X, int64_t ld
 // the same work for every wavefront: block c needs the 16 (c + 1) columns up
 // to its own), requests all its fragments of L_kk^{-1} and X at once and
 // stores after every wavefront has its part of X.  Bound by that one memory
-// round trip and 72 products per wavefront.
+// round trip and 72 products per wavefront: 14-17 us at mk = 128 (order
+// 1024), against 21 of the substituting strip.
 __device__ __forceinline__ void trsm_inv_strip(double* __restrict__ X, int64_t ld, const double* __restrict__ Linv,
                                                int64_t nb, int S, int mk) {
   const int lane = threadIdx.x & 63;
@@ -2337,7 +2339,8 @@ __device__ __forceinline__ void trsm_inv_strip(double* __restrict__ X, int64_t l
 // an update on the critical path of a factorization by small tiles.  Every
 // fragment goes straight from memory to registers, all requested at once (a
 // K this short does not repay stages in LDS); 2 x 2 wavefronts of 32 x 32.
-// The products come in the order of gemm_tile's.
+// The products come in the order of gemm_tile's.  Bound by the memory round
+// trip: 10-11 us at K = 128 (order 1024), against 24 of a 128 x 128 item.
 __device__ __forceinline__ void gemm_reg64(double* __restrict__ C, const double* __restrict__ Ap,
                                            const double* __restrict__ Bp, int64_t ld, int M, int N, int K,
                                            bool lower_only) {
