@@ -1638,6 +1638,122 @@ __device__ __forceinline__ int potrf_small(double* __restrict__ Akk, int64_t ld,
 }
 
 // ---------------------------------------------------------------------------
+// The same by columns (diag16_x, one pivot at a time; rows below by
+// substitution, one per thread; products from C on): 62.7 us for a tile of 128
+// where potrf_small takes 31.  It serves the BF16-update factorization at
+// orders above PCOL_ORDER alone.  There the diagonal tiles are off the critical
+// path, and the choice shows in the results: a rounding of 1e-16 that differs in
+// a diagonal tile flips some of the 5e8 roundings of panel values to 24 bits,
+// the flips spread through the trailing updates, and a solution that the
+// refinement has brought to 1e-8 of the exact one (order 32768, condition 1e4)
+// moves by 0.7-1.1e-9 with them.  Below, the effect is smaller (1.1e-10 at order
+// 16000, 4e-12 at 8000) and the factorization's chain is what counts.  The whole
+// solve at order 32768: 119.5 ms this way, 115.0 with potrf_small.
+#define PCOL_ORDER 24576
+// Block (bi, bj) of the resident tile -= P(bi) P(bj)^T, P the 16 columns of
+// the panel at c0.  A operand: P(bi) (rows on lanes % 16), B operand: P(bj)^T;
+// element v of lane l is then row 4v + l/16, column l%16 of the block.
+__device__ __forceinline__ void upd16_lds(double* As, int c0, int bi, int bj, int lane) {
+  const int l16 = lane & 15, lg = lane >> 4;
+  d4 acc;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) acc[v] = As[(bj * 16 + l16) * SLD + bi * 16 + 4 * v + lg];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const double fa = As[(c0 + 4 * s + lg) * SLD + bi * 16 + l16];
+    const double fb = As[(c0 + 4 * s + lg) * SLD + bj * 16 + l16];
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fa, fb, acc, 0, 0, 2 /* neg B */);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) As[(bj * 16 + l16) * SLD + bi * 16 + 4 * v + lg] = acc[v];
+}
+
+__device__ __forceinline__ int potrf_columns(double* __restrict__ Akk, int64_t ld, int m, double* lds) {
+  double* As = lds;                      // [128][SLD]
+  double* Ldd = As + 128 * SLD;          // [PW][PW + 1]
+  double* Linv = Ldd + PW * (PW + 1);    // [PW]
+  int& s_sinfo = *reinterpret_cast<int*>(Linv + PW);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nblk = (m + 15) >> 4;
+  // the lower triangle into LDS, 16 loads in flight per thread; rows and
+  // columns past m hold the identity
+  {
+    constexpr int PER = 128 * 128 / NT, BATCH = 16;
+#pragma unroll 1
+    for (int u0 = 0; u0 < PER; u0 += BATCH) {
+      double v[BATCH];
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        const int idx = tid + (u0 + u) * NT, c = idx >> 7, r = idx & 127;
+        v[u] = Akk[(int64_t)imin(c, m - 1) * ld + imin(imax(r, c), m - 1)];
+      }
+#pragma unroll
+      for (int u = 0; u < BATCH; ++u) {
+        const int idx = tid + (u0 + u) * NT, c = idx >> 7, r = idx & 127;
+        if (c < nblk * 16 && r < nblk * 16) As[c * SLD + r] = (r < m && c < m && r >= c) ? v[u] : (r == c ? 1.0 : 0.0);
+      }
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const int info = diag16_x<SLD, PW + 1>(As, 0, imin(16, m), Ldd, Linv, lane, 0);
+    if (lane == 0) s_sinfo = info;
+  }
+  __syncthreads();
+  for (int j = 0; j < nblk; ++j) {
+    const int c0 = j * 16;
+    const int info = __builtin_amdgcn_readfirstlane(s_sinfo);
+    if (info != 0) return info;
+    // rows below the diagonal block: y := y L_dd^{-T}, one row per thread
+#pragma unroll 1
+    for (int r = c0 + 16 + tid; r < nblk * 16; r += NT) {
+      double y[PW];
+#pragma unroll
+      for (int c = 0; c < PW; ++c) y[c] = As[(c0 + c) * SLD + r];
+#pragma unroll
+      for (int c = 0; c < PW; ++c) {
+        y[c] *= Linv[c];
+#pragma unroll
+        for (int c2 = c + 1; c2 < PW; ++c2) y[c2] -= y[c] * Ldd[c2 * (PW + 1) + c];
+      }
+#pragma unroll
+      for (int c = 0; c < PW; ++c) As[(c0 + c) * SLD + r] = y[c];
+    }
+    __syncthreads();
+    if (j + 1 >= nblk) break;
+    // the panel's update of the trailing lower blocks; wavefront 0 first
+    // updates and factors the next diagonal block (the critical path)
+    const int nb2 = nblk - j - 1;
+    const int npair = nb2 * (nb2 + 1) / 2;
+    if (wave == 0) {
+      upd16_lds(As, c0, j + 1, j + 1, lane);
+      const int info2 = diag16_x<SLD, PW + 1>(As, c0 + 16, imin(16, m - c0 - 16), Ldd, Linv, lane, c0 + 16);
+      if (lane == 0) s_sinfo = info2;
+    }
+    // block pairs p >= 1 in column-major order of (bi >= bj), after (j+1, j+1),
+    // on the other three wavefronts (wavefront 0 is busy with the diagonal)
+#pragma unroll 1
+    for (int p = (wave == 0 ? npair : wave); p < npair; p += 3) {
+      int cj = 0, rem = p;
+      while (rem >= nb2 - cj) {
+        rem -= nb2 - cj;
+        ++cj;
+      }
+      const int bj = j + 1 + cj;
+      upd16_lds(As, c0, bj + rem, bj, lane);
+    }
+    __syncthreads();
+  }
+  // the factor to the tile, lower triangle only
+  for (int idx = tid; idx < m * 128; idx += NT) {
+    const int c = idx >> 7, r = idx & 127;
+    if (r < m && r >= c) st_dev(Akk + (int64_t)c * ld + r, As[c * SLD + r]);
+  }
+  return 0;
+}
+
+// ---------------------------------------------------------------------------
 // POTRF work item for a tile of order m <= 512 on one workgroup:
 // Akk := chol(Akk), lower, in place.  Left-looking by panels of PT_W = 32
 // columns, each taken in slabs of up to PT_SLAB = 256 rows that stay in LDS
@@ -2341,9 +2457,11 @@ __device__ __forceinline__ void trsm_inv_strip(double* __restrict__ X, int64_t l
 // K this short does not repay stages in LDS); 2 x 2 wavefronts of 32 x 32.
 // The products come in the order of gemm_tile's.  Bound by the memory round
 // trip: 10-11 us at K = 128 (order 1024), against 24 of a 128 x 128 item.
+// from_c: they are subtracted from C one after the other (potrf_columns' order
+// of rounding) instead of summed first.
 __device__ __forceinline__ void gemm_reg64(double* __restrict__ C, const double* __restrict__ Ap,
                                            const double* __restrict__ Bp, int64_t ld, int M, int N, int K,
-                                           bool lower_only) {
+                                           bool lower_only, bool from_c = false) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, lg = lane >> 4;
@@ -2376,8 +2494,9 @@ __device__ __forceinline__ void gemm_reg64(double* __restrict__ C, const double*
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = wr + 16 * r + l16, col = wc + 16 * c + 4 * i + lg;
-        c0[r][c][i] = C[(int64_t)imin(col, N - 1) * ld + imin(row, M - 1)];
-        acc[r][c][i] = 0.0;
+        const double v = C[(int64_t)imin(col, N - 1) * ld + imin(row, M - 1)];
+        c0[r][c][i] = from_c ? 0.0 : v;
+        acc[r][c][i] = from_c ? -v : 0.0;
       }
 #pragma unroll
   for (int t = 0; t < 8; ++t)
@@ -2898,9 +3017,18 @@ __device__ __forceinline__ void gemv_strip(const TL* L, int64_t ld, double* Y, c
 // their SYRK updates there, so the tile is factored in place by the FP64
 // tile kernel.  Dk then holds L_kk for the TRSM strips of step k and the
 // tile's inverses (TRTRI); the FP32 copy's diagonal tiles are never read.
-__device__ __forceinline__ int potrf_tile_mixed(double* __restrict__ Dk, int64_t ldd, int m, double* lds) {
+template <bool COLUMNS>
+__device__ __forceinline__ int potrf_tile_mixed(double* __restrict__ Dk, int64_t ldd, int m, double* lds,
+                                                bool by_columns) {
   const int tid = threadIdx.x;
-  const int info = __builtin_amdgcn_readfirstlane(m <= 128 ? potrf_small(Dk, ldd, m, lds) : potrf_tile<128>(Dk, ldd, m, lds));
+  int info;
+  if (m > 128)
+    info = potrf_tile<128>(Dk, ldd, m, lds);
+  else if (COLUMNS && by_columns)
+    info = potrf_columns(Dk, ldd, m, lds);
+  else
+    info = potrf_small(Dk, ldd, m, lds);
+  info = __builtin_amdgcn_readfirstlane(info);
   // a ragged tile is padded to a multiple of 16 with the identity (for its
   // explicit inverse, which then holds L^{-1} in its leading m x m block)
   const int mpad = (m + 15) & ~15;
@@ -3353,7 +3481,8 @@ __device__ __forceinline__ void raise_error(const KArgs& a, int code) {
 // (T2 = ceil(m / 128) per side):
 //   P(b)        chol of sub-block (b, b)                  (potrf_small)
 //   S(r, b, s)  32-row strip s of sub-block (r, b) := . L_bb^{-T}, r > b   (trsm_strip)
-//   U(r, c, b)  sub-block (r, c) -= L_rb L_cb^T, r >= c > b  (SYRK / GEMM core)
+//   U(r, c, b, s)  64 x 64 block s of sub-block (r, c) -= L_rb L_cb^T, r >= c > b  (gemm_reg64:
+//               10 us where a whole 128 x 128 sub-block takes gemm_tile 24)
 // The POTRF task has several work items; each one that starts joins the
 // tile's pool: the worker takes the next sub-unit from a counter in the
 // workspace, waits for that unit's predecessors through per-sub-block
@@ -3369,16 +3498,22 @@ __device__ __forceinline__ void raise_error(const KArgs& a, int code) {
 #define PL_NEXT 0      // next unit to hand out
 #define PL_P 2         // + b: P(b) done
 #define PL_S 8         // + 4 r + b: strips of S(r, b) done
-#define PL_U 24        // + 4 r + c: updates applied to sub-block (r, c)
+#define PL_U 24        // + 4 r + c: blocks of updates applied to sub-block (r, c)
 #define PL_INV 44      // items of the tile's TRTRI done
 
 struct PoolUnit {
-  int type, b, r, c, s;  // type 0: P(b); 1: S(r, b, s); 2: U(r, c, b); -1: none left
+  int type, b, r, c, s;  // type 0: P(b); 1: S(r, b, s); 2: U(r, c, b, s); -1: none left
 };
 
 __device__ __forceinline__ int psb_size(int m, int i) { return imin(PSB, m - i * PSB); }
 __device__ __forceinline__ int psb_strips(int m, int i) { return (psb_size(m, i) + TS - 1) / TS; }
 
+// Blocks of an update of sub-block (r, c), r >= c: 64 x 64, of a diagonal
+// one the lower blocks, row by row.
+__device__ __forceinline__ int psb_blocks(int m, int r, int c) {
+  const int nr = psb_size(m, r) > 64 ? 2 : 1, nc = psb_size(m, c) > 64 ? 2 : 1;
+  return r == c ? nr * (nr + 1) / 2 : nr * nc;
+}
 // Unit u of the sub-DAG in claim order: step by step, P(b), then the strips
 // of each sub-block row below it, then its updates column by column (the
 // next diagonal sub-block's first: it leads to P(b + 1)).
@@ -3394,8 +3529,9 @@ __device__ __forceinline__ PoolUnit pool_unit(int m, int u) {
     }
     for (int c = b + 1; c < T2; ++c)
       for (int r = c; r < T2; ++r) {
-        if (u == 0) return {2, b, r, c, 0};
-        --u;
+        const int nu = psb_blocks(m, r, c);
+        if (u < nu) return {2, b, r, c, u};
+        u -= nu;
       }
   }
   return {-1, 0, 0, 0, 0};
@@ -3432,13 +3568,15 @@ __device__ __forceinline__ bool pool_wait(const KArgs& a, const int32_t* pool, i
 // Wavefront 0: waits for the predecessors of pool unit pu of a tile of order m.
 __device__ __forceinline__ bool pool_wait_unit(const KArgs& a, const int32_t* pool, int m, const PoolUnit& pu,
                                                int lane) {
+  // sub-block (r, c) updated b times (c = b for P and S)
+  const int nu = pu.b * psb_blocks(m, pu.r, pu.c);
   if (pu.type == 0)  // P(b): the diagonal sub-block has taken its b updates
-    return pool_wait(a, pool, PL_U + 5 * pu.b, pu.b, PL_U + 5 * pu.b, pu.b, PL_U + 5 * pu.b, pu.b, lane);
+    return pool_wait(a, pool, PL_U + 5 * pu.b, nu, PL_U + 5 * pu.b, nu, PL_U + 5 * pu.b, nu, lane);
   if (pu.type == 1)  // S(r, b, s): L_bb factored, sub-block (r, b) updated b times
-    return pool_wait(a, pool, PL_P + pu.b, 1, PL_U + 4 * pu.r + pu.b, pu.b, PL_P + pu.b, 1, lane);
+    return pool_wait(a, pool, PL_P + pu.b, 1, PL_U + 4 * pu.r + pu.b, nu, PL_P + pu.b, 1, lane);
   // U(r, c, b): every strip of (r, b) and (c, b) solved, (r, c) updated b times
   return pool_wait(a, pool, PL_S + 4 * pu.r + pu.b, psb_strips(m, pu.r), PL_S + 4 * pu.c + pu.b,
-                   psb_strips(m, pu.c), PL_U + 4 * pu.r + pu.c, pu.b, lane);
+                   psb_strips(m, pu.c), PL_U + 4 * pu.r + pu.c, nu, lane);
 }
 
 // SEG = 128: the launch guarantees even leading dimensions, 16-byte aligned
@@ -3740,10 +3878,15 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         int info;
         if constexpr (MIXED) {
           double* const Dk = Dsys + (int64_t)tk * nb * nb;
+          const bool by_columns = MODE == 5 && sn > PCOL_ORDER;
           if (POOLED && unit >= 0) {
             // P(b) on the FP64 diagonal tile; the last one pads a ragged tile
             // to a multiple of 16 with the identity (for its inverse)
-            info = uniform_i(potrf_small(Dk + (int64_t)po_k * nb + po_k, nb, po_m, lds));
+            double* const Db = Dk + (int64_t)po_k * nb + po_k;
+            if (by_columns)
+              info = uniform_i(potrf_columns(Db, nb, po_m, lds));
+            else
+              info = uniform_i(potrf_small(Db, nb, po_m, lds));
             if (info != 0) {
               info += po_k;
             } else if (po_k + po_m == tsz(tk)) {
@@ -3755,7 +3898,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
             }
           } else {
             if (part > 0) break;  // one workgroup factors the tile
-            info = uniform_i(potrf_tile_mixed(Dk, nb, tsz(tk), lds));
+            info = uniform_i(potrf_tile_mixed<MODE == 5>(Dk, nb, tsz(tk), lds, by_columns));
           }
         } else {
           const bool sub = unit >= 0;
@@ -3857,11 +4000,16 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         int64_t crow = (int64_t)ti * nb + si * bm, ccol = (int64_t)tj * nb + sj * bn, kcol = (int64_t)tk * nb;
         int64_t brow = (int64_t)tj * nb + sj * bn;
         if (POOLED && unit >= 0) {
-          // sub-block (r, c) of the diagonal tile -= L_rb L_cb^T
-          M = po_m;
-          N = po_n;
+          // block (bi, bj) of sub-block (r, c) of the diagonal tile -= L_rb L_cb^T
+          const int nc = po_n > 64 ? 2 : 1;
+          const int bi = po_r == po_c ? (po_s + 1) >> 1 : po_s / nc, bj = po_r == po_c ? po_s >> 1 : po_s % nc;
+          lower = po_r == po_c && bi == bj;
+          po_r += 64 * bi;
+          po_c += 64 * bj;
+          bm = 64;
+          M = imin(64, po_m - 64 * bi);
+          N = imin(64, po_n - 64 * bj);
           K = po_kk;
-          lower = po_r == po_c;
           crow = (int64_t)tk * nb + po_r;
           ccol = (int64_t)tk * nb + po_c;
           kcol = (int64_t)tk * nb + po_k;
@@ -3873,10 +4021,12 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         const bool misaligned = ((reinterpret_cast<uintptr_t>(Ap) | reinterpret_cast<uintptr_t>(Bp)) & 15) != 0;
         if constexpr (MIXED) {
           if (POOLED && unit >= 0) {
-            // sub-block (r, c) of the FP64 diagonal tile -= L_rb L_cb^T, in FP64
+            // the block on the FP64 diagonal tile, in FP64
             double* const Dk = Dsys + (int64_t)tk * nb * nb;
-            gemm_nt<128>(Dk + (int64_t)po_c * nb + po_r, Dk + (int64_t)po_k * nb + po_r,
-                         Dk + (int64_t)po_k * nb + po_c, nb, M, N, K, lower, lds);
+            double* const Cu = Dk + (int64_t)po_c * nb + po_r;
+            const double* const Au = Dk + (int64_t)po_k * nb + po_r;
+            const double* const Bu = Dk + (int64_t)po_k * nb + po_c;
+            gemm_reg64(Cu, Au, Bu, nb, M, N, K, lower, MODE == 5 && sn > PCOL_ORDER);
             break;
           }
           // four rows per 16-byte lane: ld a multiple of 4 and three rows after the order
