@@ -65,15 +65,23 @@ __device__ __forceinline__ double readlane_f64(double v, int l) {
 // products.  Issued this way the compiler does not track them at all, and
 // every consumer waits for them explicitly (vmcnt counts, then a workgroup
 // barrier) before reading the stage they fill.  M0 is set in the same
-// statement, right before the load; it is a reserved register the compiler
-// sets itself before each of its own uses (these kernels have none).
+// statement; it is a reserved register the compiler sets itself before each of
+// its own uses (these kernels have none).
+//
+// The wait states that the compiler adds to its own code are missing inside an
+// assembly statement, so each statement brings them along: one instruction
+// between the scalar write of M0 and the transfer that reads it, and a base in
+// scalar registers that a scalar instruction of the statement wrote (a copy to
+// VCC).  The base itself often comes from a readfirstlane or from a spilled
+// scalar, which are vector instructions, and a memory instruction may read a
+// scalar register only five wait states after a vector instruction wrote it.
 // (the low word of a generic pointer into LDS is the LDS byte address; a cast
 // of the pointer to LDS would add a test for null to every transfer)
 __device__ __forceinline__ uint32_t lds_addr(double* l) {
   return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)l);
 }
 __device__ __forceinline__ void dma16(const void* g, double* l) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr(l)), "v"(g) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_addr(l)), "v"(g) : "memory");
 }
 // The same from a wave-uniform base (scalar registers) plus a per-lane byte
 // offset below 4 GB: one 32-bit register per lane instead of a 64-bit address.
@@ -83,25 +91,25 @@ __device__ __forceinline__ const void* uniform_ptr(const void* p) {
   return (const void*)(uintptr_t)(((uint64_t)hi << 32) | lo);
 }
 __device__ __forceinline__ void dma16s(const void* base, uint32_t off, double* l) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_addr(l)), "v"(off), "s"(uniform_ptr(base))
-               : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 vcc, %2\n\tglobal_load_lds_dwordx4 %1, vcc"
+               : : "s"(lds_addr(l)), "v"(off), "s"(uniform_ptr(base)) : "memory", "vcc");
 }
 __device__ __forceinline__ void dma4s(const void* base, uint32_t off, double* l) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" : : "s"(lds_addr(l)), "v"(off), "s"(uniform_ptr(base))
-               : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 vcc, %2\n\tglobal_load_lds_dword %1, vcc"
+               : : "s"(lds_addr(l)), "v"(off), "s"(uniform_ptr(base)) : "memory", "vcc");
 }
 
 // The same with the LDS address as a wave-uniform byte address plus a
-// constant, one scalar add in all.
+// constant, one scalar add.
 template <int IMM>
 __device__ __forceinline__ void dma16i(uint64_t base, uint32_t off, uint32_t l) {
-  asm volatile("s_add_u32 m0, %0, %1\n\tglobal_load_lds_dwordx4 %2, %3" : : "s"(l), "n"(IMM), "v"(off), "s"(base)
-               : "memory", "scc");
+  asm volatile("s_add_u32 m0, %0, %1\n\ts_mov_b64 vcc, %3\n\tglobal_load_lds_dwordx4 %2, vcc"
+               : : "s"(l), "n"(IMM), "v"(off), "s"(base) : "memory", "scc", "vcc");
 }
 template <int IMM>
 __device__ __forceinline__ void dma4i(uint64_t base, uint32_t off, uint32_t l) {
-  asm volatile("s_add_u32 m0, %0, %1\n\tglobal_load_lds_dword %2, %3" : : "s"(l), "n"(IMM), "v"(off), "s"(base)
-               : "memory", "scc");
+  asm volatile("s_add_u32 m0, %0, %1\n\ts_mov_b64 vcc, %3\n\tglobal_load_lds_dword %2, vcc"
+               : : "s"(l), "n"(IMM), "v"(off), "s"(base) : "memory", "scc", "vcc");
 }
 
 constexpr int imin_c(int a, int b) { return a < b ? a : b; }
@@ -406,7 +414,7 @@ __device__ __forceinline__ void gemm_core(const double* __restrict__ C, const do
 //  - a chunk has landed one whole chunk before its products start, so the
 //    first fragments of the next chunk are read under the current one's last
 //    products, and the barrier between them finds the next products ready;
-//  - a transfer costs four scalar-side instructions (a running pointer per
+//  - a transfer costs five scalar-side instructions (a running pointer per
 //    panel, the LDS address from one base), and what a k-step issues besides
 //    its products is spread between them in small groups: a wavefront issues
 //    in order, and whatever takes longer than the product before it leaves
@@ -924,7 +932,7 @@ __device__ __forceinline__ void gemm_nt_f32_d(double* Cd, int64_t ldcd, const fl
 // rows hit distinct banks); a row group's blocks follow each other along a
 // column block (nc of them), gs bytes from one row group to the next, hblk
 // from one column block to the next and hterm from one term to the next.  A
-// transfer is then one contiguous KB at a running scalar pointer, four
+// transfer is then one contiguous KB at a running scalar pointer, five
 // instructions in all: with the rows of a K-contiguous layout (64-byte pieces,
 // a 64-bit address per lane) the 18 transfers of a chunk took twice as long to
 // issue as its products to run.

@@ -1,0 +1,50 @@
+"""Rules of the device source that no result shows reliably, checked on its text (no GPU)."""
+import glob
+import os
+import re
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1402_6601_amd", "csrc")
+HIP = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
+
+
+def _asm_statements(path):
+    """The instruction lists of the inline assembly statements of a source file."""
+    text = open(path).read()
+    out = []
+    for m in re.finditer(r'\basm\s+volatile\s*\(\s*((?:"(?:[^"\\]|\\.)*"\s*)+)', text):
+        body = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', m.group(1)))
+        out.append([i.strip() for i in re.split(r"\\n(?:\\t)?|;", body) if i.strip()])
+    return out
+
+
+def _wait_states(ins):
+    m = re.match(r"s_nop\s+(\w+)", ins)
+    return int(m.group(1), 0) + 1 if m else 1
+
+
+@pytest.mark.parametrize("path", HIP, ids=os.path.basename)
+def test_wait_states_before_lds_transfers(path):
+    """What the compiler sees to in its own code, but not inside assembly: a
+    scalar write of M0 and the transfer into LDS that reads it are one wait state
+    apart; and a transfer's scalar base, which a vector instruction
+    (readfirstlane, the restore of a spilled scalar) may have written right before
+    the statement, is copied by a scalar instruction of the statement or read
+    five wait states after its start."""
+    found = 0
+    for ins in _asm_statements(path):
+        for at, b in enumerate(ins):
+            if "_lds_" not in b:
+                continue
+            found += 1
+            before = ins[:at]
+            m0 = [k for k, a in enumerate(before) if re.match(r"s_\w+\s+m0\b", a)]
+            assert m0 and sum(_wait_states(a) for a in before[m0[-1] + 1:]) >= 1, ins
+            base = b.split(",")[-1].strip()
+            if base != "off":
+                copied = any(re.match(r"s_\w+\s+%s\b" % re.escape(base), a) for a in before)
+                assert copied or sum(_wait_states(a) for a in before) >= 5, ins
+    if path.endswith("tchol_device.hip"):
+        assert found >= 5  # the transfers are still found
