@@ -3623,6 +3623,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
   constexpr bool COMPACT = MODE == 6 || MODE == 7;
   __shared__ double lds[COMPACT ? LDS_COMPACT_DOUBLES : LDS_DOUBLES];
   __shared__ int s_claim[6];
+  __shared__ int s_late;  // the outcome of a late wait (the claim's words stay as they were claimed)
   __shared__ int32_t s_desc[DESC_WORDS];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = uniform_i(tid >> 6);
@@ -3825,12 +3826,12 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         const bool go = wait_ready(a, task, lane, nullptr, f, []() __attribute__((always_inline)) { return false; });
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         if (lane == 0) {
-          s_claim[5] = go;
+          s_late = go;
           if (a.trace) a.trace[4 * (int64_t)ticket + 1] = wall_clock64();
         }
       }
       lds_barrier();
-      const bool go = uniform_i(s_claim[5]) != 0;
+      const bool go = uniform_i(s_late) != 0;
       if (!go) ok = 0;
       return go;
     };

@@ -48,3 +48,12 @@ def test_wait_states_before_lds_transfers(path):
                 assert copied or sum(_wait_states(a) for a in before) >= 5, ins
     if path.endswith("tchol_device.hip"):
         assert found >= 5  # the transfers are still found
+
+
+def test_claim_words_have_one_writer():
+    """Every wavefront reads the words of a claim after its barrier, at its own
+    time: nothing but the claim stores them, so that no wavefront can find a word
+    that another one has gone on to overwrite."""
+    text = open(os.path.join(CSRC, "tchol_device.hip")).read()
+    stores = re.findall(r"\bs_claim\[(\w+)\]\s*=(?!=)", text)
+    assert len(stores) >= 6 and sorted(set(stores)) == sorted(stores), stores
