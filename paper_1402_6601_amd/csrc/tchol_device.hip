@@ -3508,6 +3508,10 @@ __device__ __forceinline__ void raise_error(const KArgs& a, int code) {
 #define PL_S 8         // + 4 r + b: strips of S(r, b) done
 #define PL_U 24        // + 4 r + c: blocks of updates applied to sub-block (r, c)
 #define PL_INV 44      // items of the tile's TRTRI done
+// A unit that failed, or was skipped in a launch in which a failing system
+// stops only its own work, adds PL_FAILED to its counter as well: the units that
+// wait for it find out with the wait, and are skipped too.
+#define PL_FAILED 0x10000
 
 struct PoolUnit {
   int type, b, r, c, s;  // type 0: P(b); 1: S(r, b, s); 2: U(r, c, b, s); -1: none left
@@ -3548,14 +3552,18 @@ __device__ __forceinline__ PoolUnit pool_unit(int m, int u) {
 // Wavefront 0: waits until pool[q0] >= v0, pool[q1] >= v1 and pool[q2] >= v2
 // (agent-scope loads, s_sleep back-off); false on abort or when the wait
 // exceeds its bound (which then raises TCHOL_E_TIMEOUT like a task wait).
+// failed: set when a unit counted there was one (PL_FAILED).
 __device__ __forceinline__ bool pool_wait(const KArgs& a, const int32_t* pool, int q0, int v0, int q1, int v1, int q2,
-                                          int v2, int lane) {
+                                          int v2, int lane, int& failed) {
   // the three counters and the abort flag in flight together: one round trip per poll
   int ab = 0;
   auto met = [&]() __attribute__((always_inline)) {
     const int x0 = ld_relaxed(pool + q0), x1 = ld_relaxed(pool + q1), x2 = ld_relaxed(pool + q2);
     ab = uniform_i(ld_relaxed(&a.hdr[HDR_ABORT]));
-    return uniform_i((x0 >= v0) & (x1 >= v1) & (x2 >= v2)) != 0;
+    constexpr int count = PL_FAILED - 1;
+    const bool all = uniform_i(((x0 & count) >= v0) & ((x1 & count) >= v1) & ((x2 & count) >= v2)) != 0;
+    if (all && uniform_i(x0 | x1 | x2) >= PL_FAILED) failed = 1;
+    return all;
   };
   if (met()) return ab == 0;
   const uint64_t t0 = wall_clock64();
@@ -3575,16 +3583,16 @@ __device__ __forceinline__ bool pool_wait(const KArgs& a, const int32_t* pool, i
 
 // Wavefront 0: waits for the predecessors of pool unit pu of a tile of order m.
 __device__ __forceinline__ bool pool_wait_unit(const KArgs& a, const int32_t* pool, int m, const PoolUnit& pu,
-                                               int lane) {
+                                               int lane, int& failed) {
   // sub-block (r, c) updated b times (c = b for P and S)
   const int nu = pu.b * psb_blocks(m, pu.r, pu.c);
   if (pu.type == 0)  // P(b): the diagonal sub-block has taken its b updates
-    return pool_wait(a, pool, PL_U + 5 * pu.b, nu, PL_U + 5 * pu.b, nu, PL_U + 5 * pu.b, nu, lane);
+    return pool_wait(a, pool, PL_U + 5 * pu.b, nu, PL_U + 5 * pu.b, nu, PL_U + 5 * pu.b, nu, lane, failed);
   if (pu.type == 1)  // S(r, b, s): L_bb factored, sub-block (r, b) updated b times
-    return pool_wait(a, pool, PL_P + pu.b, 1, PL_U + 4 * pu.r + pu.b, nu, PL_P + pu.b, 1, lane);
+    return pool_wait(a, pool, PL_P + pu.b, 1, PL_U + 4 * pu.r + pu.b, nu, PL_P + pu.b, 1, lane, failed);
   // U(r, c, b): every strip of (r, b) and (c, b) solved, (r, c) updated b times
   return pool_wait(a, pool, PL_S + 4 * pu.r + pu.b, psb_strips(m, pu.r), PL_S + 4 * pu.c + pu.b,
-                   psb_strips(m, pu.c), PL_U + 4 * pu.r + pu.c, nu, lane);
+                   psb_strips(m, pu.c), PL_U + 4 * pu.r + pu.c, nu, lane, failed);
 }
 
 // SEG = 128: the launch guarantees even leading dimensions, 16-byte aligned
@@ -3635,6 +3643,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
   // wavefront 0: the POTRF pool this worker serves (pl_task < 0: none) and
   // the POTRF work item's record, published when the pool has run dry
   int pl_task = -1, pl_m = 0, pl_ticket = 0, pl_parts = 0, pl_e0 = 0, pl_e1 = 0;
+  int pl_failed = 0;  // the system had failed when this worker joined the pool
   int32_t* pl_pool = nullptr;
   // a launch of one matrix (nsys <= 2: its factor's and its solve's tile size)
   // keeps the system records in LDS and has one failure word, which the claim
@@ -3662,7 +3671,8 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
           task = pl_task;
           t = pl_ticket;
           unit = u;
-          if (!pool_wait_unit(a, pl_pool, pl_m, pu, lane)) task = -1;
+          failed = pl_failed;
+          if (!pool_wait_unit(a, pl_pool, pl_m, pu, lane, failed)) task = -1;
         } else {
           // the pool has run dry: this worker's POTRF work item is complete
           p_task = pl_task;
@@ -3744,6 +3754,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
             pl_pool = a.pool + POOL_WORDS * (srd[6] + tkd);
             pl_ticket = t;
             pl_parts = pd;
+            pl_failed = failed;
             pl_e0 = uniform_i(__builtin_amdgcn_readlane(dv, 5));
             pl_e1 = uniform_i(__builtin_amdgcn_readlane(dv, 6));
             int u = 0;
@@ -3752,7 +3763,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
             const PoolUnit pu = pool_unit(pl_m, u);
             if (pu.type >= 0) {
               unit = u;
-              if (!pool_wait_unit(a, pl_pool, pl_m, pu, lane)) task = -1;
+              if (!pool_wait_unit(a, pl_pool, pl_m, pu, lane, failed)) task = -1;
             } else {
               unit = -2;  // the pool ran dry before this item started: nothing to do
               pl_task = -1;
@@ -3835,6 +3846,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
       if (!go) ok = 0;
       return go;
     };
+    int unit_failed = skip;
     int count_inv = 0;  // a TRTRI item of an FP64 launch counts up its tile's pool word
     // A unit of a POTRF pool runs the POTRF, TRSM or GEMM body on sub-blocks
     // of the diagonal tile (tk, tk): po_* give the sub-block offsets (rows,
@@ -3932,6 +3944,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
           }
         }
         if (info != 0 && !a.batched) ok = 0;
+        if (info != 0 && a.batched) unit_failed = 1;
         break;
       }
       case TK_TRSM: {
@@ -4277,8 +4290,8 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
       // a pool unit: its sub-block counter tells the units that wait for it
       if (tid == 0) {
         const int ctr = pu.type == 0 ? PL_P + pu.b : (pu.type == 1 ? PL_S + 4 * pu.r + pu.b : PL_U + 4 * pu.r + pu.c);
-        __hip_atomic_fetch_add(a.pool + POOL_WORDS * (sr[6] + tk) + ctr, 1, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(a.pool + POOL_WORDS * (sr[6] + tk) + ctr, unit_failed ? 1 + PL_FAILED : 1,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     } else if (wave == 0) {
       if (count_inv && lane == 0)
