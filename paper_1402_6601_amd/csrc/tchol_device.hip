@@ -3631,7 +3631,9 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
   constexpr bool COMPACT = MODE == 6 || MODE == 7;
   __shared__ double lds[COMPACT ? LDS_COMPACT_DOUBLES : LDS_DOUBLES];
   __shared__ int s_claim[6];
-  __shared__ int s_late;  // the outcome of a late wait (the claim's words stay as they were claimed)
+  // what wavefront 0 finds out after the claim: whether the item's system has
+  // failed, the outcome of a late wait (the claim's words stay as they were claimed)
+  __shared__ int s_word;
   __shared__ int32_t s_desc[DESC_WORDS];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = uniform_i(tid >> 6);
@@ -3826,7 +3828,23 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
     };
     // in a batched launch a system whose factorization failed only passes
     // its remaining tasks on, so that the DAG drains
-    const bool skip = one_matrix ? uniform_i(s_claim[4]) != 0 : a.batched && uniform_i(ld_relaxed(&a.sinfo[sid])) != 0;
+    // (one read for the whole workgroup, whose wavefronts must agree while
+    // another one may be storing the word: a single matrix's came with the
+    // claim.  In the compact instance a system's tasks follow one another, and
+    // every wavefront that loads the word finds the same.)
+    bool skip;
+    if (COMPACT) {
+      skip = uniform_i(ld_relaxed(&a.sinfo[sid])) != 0;
+    } else if (one_matrix) {
+      skip = uniform_i(s_claim[4]) != 0;
+    } else {
+      if (wave == 0) {
+        const int f = ld_relaxed(&a.sinfo[sid]);
+        if (lane == 0) s_word = f;
+      }
+      lds_barrier();
+      skip = uniform_i(s_word) != 0;
+    }
     int ok = 1;
     // the wait of a strip that was claimed early (all wavefronts): false when the run is being aborted
     const bool was_early = uniform_i(s_claim[5]) != 0;
@@ -3837,12 +3855,12 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         const bool go = wait_ready(a, task, lane, nullptr, f, []() __attribute__((always_inline)) { return false; });
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         if (lane == 0) {
-          s_late = go;
+          s_word = go;
           if (a.trace) a.trace[4 * (int64_t)ticket + 1] = wall_clock64();
         }
       }
       lds_barrier();
-      const bool go = uniform_i(s_late) != 0;
+      const bool go = uniform_i(s_word) != 0;
       if (!go) ok = 0;
       return go;
     };

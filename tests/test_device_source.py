@@ -57,3 +57,16 @@ def test_claim_words_have_one_writer():
     text = open(os.path.join(CSRC, "tchol_device.hip")).read()
     stores = re.findall(r"\bs_claim\[(\w+)\]\s*=(?!=)", text)
     assert len(stores) >= 6 and sorted(set(stores)) == sorted(stores), stores
+
+
+def test_wavefronts_agree_on_skipping():
+    """Whether a work item is skipped is read once per workgroup, by the claim: a
+    load by every wavefront could find a failure word that another workgroup
+    changes in between, and the wavefronts' barriers would not match.  (The
+    compact instance may load it anywhere: its systems' tasks follow each other.)"""
+    text = open(os.path.join(CSRC, "tchol_device.hip")).read()
+    loads = [l.strip() for l in text.splitlines() if re.search(r"ld_relaxed\(&a\.sinfo\[", l)]
+    assert loads
+    for at in re.finditer(r"ld_relaxed\(&a\.sinfo\[", text):
+        guard = text[max(0, at.start() - 60):at.start()]
+        assert re.search(r"if \((wave == 0|COMPACT)\) \{\s*[^{}]*$", guard), guard

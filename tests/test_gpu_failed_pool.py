@@ -20,7 +20,7 @@ def tc():
 
 
 @pytest.mark.parametrize("n,nb", [(500, 192), (700, 208), (1000, 448), (600, 320)])
-@pytest.mark.parametrize("call", ["inverses", "substitution", "random order", "batch of one"])
+@pytest.mark.parametrize("call", ["inverses", "substitution", "random order", "batch of one", "batch of three"])
 def test_nothing_after_the_failed_sub_block(tc, n, nb, call):
     print("case n=%d nb=%d %s" % (n, nb, call), flush=True)
     A, b = spd_inputs.spd_matrix_and_rhs(n, nb, nrhs=2)
