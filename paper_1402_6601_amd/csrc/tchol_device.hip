@@ -1233,8 +1233,8 @@ __device__ __forceinline__ double quad_to_row(double v) {
 }
 
 struct Quad {
-  double fw;      // the solve operand
-  double d[4], y[4];  // the pivots and their reciprocal square roots
+  double fw;    // the solve operand
+  double d[4];  // the pivots
 };
 
 template <int S>
@@ -1261,7 +1261,6 @@ __device__ __forceinline__ unsigned quad_factor(double xs, const double (&e)[4],
     const double er = fma(-(d * y0), y0, 1.0);
     const double y = fma(y0 * er, fma(0.375, er, 0.5), y0);
     q.d[c] = d;
-    q.y[c] = y;
 #pragma unroll
     for (int i = c + 1; i < 4; ++i) {
       double v = a[ix(i, c)];
@@ -1284,11 +1283,14 @@ __device__ __forceinline__ unsigned quad_factor(double xs, const double (&e)[4],
 #define QUAD_OPS 10
 __device__ __forceinline__ constexpr int quad_op(int s, int i) { return s == i ? s : 4 + (s == 0 ? i - 1 : s == 1 ? i + 1 : 5); }
 
-// One sub-step on the diagonal block xd (L's columns to lf) and one row
-// block x of the panel.  e[c] = (l / 16 == c).  Its operands also go to Fb.
+// One sub-step on the diagonal block xd (L's columns below the diagonal to lf)
+// and one row block x of the panel.  e[c] = (l / 16 == c).  Its operands also go
+// to Fb; the lanes that hold L's diagonal take the pivot to dv and its
+// reciprocal square root, the diagonal of the solve operand, to yv.
 // Returns as quad_factor.
 template <int S>
-__device__ __forceinline__ unsigned panel_quad(d4& xd, d4& lf, d4& x, const double (&e)[4], int lane, double* Fb) {
+__device__ __forceinline__ unsigned panel_quad(d4& xd, d4& lf, d4& x, const double (&e)[4], int lane, double* Fb,
+                                               double& dv, double& yv) {
   const int l16 = lane & 15;
   Quad q;
   const unsigned bad = quad_factor<S>(xd[S], e, l16, q);
@@ -1309,10 +1311,10 @@ __device__ __forceinline__ unsigned panel_quad(d4& xd, d4& lf, d4& x, const doub
     xd[S + 3] = mfma4_f64_neg(yq[S + 3], zd, xd[S + 3]);
   }
   xd[S] = zd;
-  double v = zd;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) v = (lane == 16 * c + 4 * S + c) ? q.d[c] * q.y[c] : v;
-  lf[S] = v;
+  for (int c = 0; c < 4; ++c) dv = (lane == 16 * c + 4 * S + c) ? q.d[c] : dv;
+  yv = (l16 >> 2) == S ? q.fw : yv;
+  lf[S] = zd;
   x[S] = z;
 #pragma unroll
   for (int i = S + 1; i < 4; ++i) {
@@ -1328,10 +1330,22 @@ __device__ __forceinline__ unsigned panel_quad(d4& xd, d4& lf, d4& x, const doub
 // pivot that is not positive.
 __device__ __forceinline__ int panel16(d4& xd, d4& lf, d4& x, const double (&e)[4], int lane, int ibase,
                                        double* Fb) {
-  unsigned bad = panel_quad<0>(xd, lf, x, e, lane, Fb);
-  bad |= panel_quad<1>(xd, lf, x, e, lane, Fb);
-  bad |= panel_quad<2>(xd, lf, x, e, lane, Fb);
-  bad |= panel_quad<3>(xd, lf, x, e, lane, Fb);
+  double dv = 1.0, yv = 1.0;
+  unsigned bad = panel_quad<0>(xd, lf, x, e, lane, Fb, dv, yv);
+  bad |= panel_quad<1>(xd, lf, x, e, lane, Fb, dv, yv);
+  bad |= panel_quad<2>(xd, lf, x, e, lane, Fb, dv, yv);
+  bad |= panel_quad<3>(xd, lf, x, e, lane, Fb, dv, yv);
+  // L's diagonal, all sixteen at once (each on the lane that holds it): d times
+  // its reciprocal root, with one correction of the residual d - l^2, which for
+  // a pivot near the smallest numbers is taken at 2^1000 times its size
+  const bool tiny = dv < 0x1p-900;
+  const double ds = tiny ? dv * 0x1p+1000 : dv, ys = tiny ? yv * 0x1p-500 : yv;
+  double l = ds * ys;
+  l = fma(fma(-l, l, ds), 0.5 * ys, l);
+  l = tiny ? l * 0x1p-500 : l;
+  const int l16 = lane & 15, lg = lane >> 4;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) lf[s] = l16 == 4 * s + lg ? l : lf[s];
   return bad ? ibase + __builtin_ctz(bad) + 1 : 0;
 }
 
