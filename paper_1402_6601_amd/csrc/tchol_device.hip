@@ -1662,16 +1662,15 @@ __device__ __forceinline__ int potrf_small(double* __restrict__ Akk, int64_t ld,
 // ---------------------------------------------------------------------------
 // The same by columns (diag16_x, one pivot at a time; rows below by
 // substitution, one per thread; products from C on): 62.7 us for a tile of 128
-// where potrf_small takes 31.  It serves the BF16-update factorization at
-// orders above PCOL_ORDER alone.  There the diagonal tiles are off the critical
-// path, and the choice shows in the results: a rounding of 1e-16 that differs in
-// a diagonal tile flips some of the 5e8 roundings of panel values to 24 bits,
-// the flips spread through the trailing updates, and a solution that the
-// refinement has brought to 1e-8 of the exact one (order 32768, condition 1e4)
-// moves by 0.7-1.1e-9 with them.  Below, the effect is smaller (1.1e-10 at order
-// 16000, 4e-12 at 8000) and the factorization's chain is what counts.  The whole
-// solve at order 32768: 119.5 ms this way, 115.0 with potrf_small.
-#define PCOL_ORDER 24576
+// where potrf_small takes 31.  It serves the BF16-update factorization alone,
+// whose results depend on the order of rounding: a rounding of 1e-16 that differs
+// in a diagonal tile flips some of the roundings of panel values to 24 bits, the
+// flips spread through the trailing updates, and a solution moves with them, by
+// 1e-12 at order 4000, 1e-10 at 16000 and up to 1.1e-9 at 32768 (condition
+// 1e4, where the refinement leaves it 1e-8 from the exact one).  This order of
+// rounding keeps the solutions that the factorization has always had.  The whole
+// solve this way / with potrf_small: order 4000 8.4 / 7.0 ms, 8192 15.9 / 12.9,
+// 16000 32.3 / 27.2, 32768 118.8 / 114.4.
 // Block (bi, bj) of the resident tile -= P(bi) P(bj)^T, P the 16 columns of
 // the panel at c0.  A operand: P(bi) (rows on lanes % 16), B operand: P(bj)^T;
 // element v of lane l is then row 4v + l/16, column l%16 of the block.
@@ -3039,14 +3038,13 @@ __device__ __forceinline__ void gemv_strip(const TL* L, int64_t ld, double* Y, c
 // their SYRK updates there, so the tile is factored in place by the FP64
 // tile kernel.  Dk then holds L_kk for the TRSM strips of step k and the
 // tile's inverses (TRTRI); the FP32 copy's diagonal tiles are never read.
-template <bool COLUMNS>
-__device__ __forceinline__ int potrf_tile_mixed(double* __restrict__ Dk, int64_t ldd, int m, double* lds,
-                                                bool by_columns) {
+template <bool BY_COLUMNS>
+__device__ __forceinline__ int potrf_tile_mixed(double* __restrict__ Dk, int64_t ldd, int m, double* lds) {
   const int tid = threadIdx.x;
   int info;
   if (m > 128)
     info = potrf_tile<128>(Dk, ldd, m, lds);
-  else if (COLUMNS && by_columns)
+  else if constexpr (BY_COLUMNS)
     info = potrf_columns(Dk, ldd, m, lds);
   else
     info = potrf_small(Dk, ldd, m, lds);
@@ -3931,12 +3929,11 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
         int info;
         if constexpr (MIXED) {
           double* const Dk = Dsys + (int64_t)tk * nb * nb;
-          const bool by_columns = MODE == 5 && sn > PCOL_ORDER;
           if (POOLED && unit >= 0) {
             // P(b) on the FP64 diagonal tile; the last one pads a ragged tile
             // to a multiple of 16 with the identity (for its inverse)
             double* const Db = Dk + (int64_t)po_k * nb + po_k;
-            if (by_columns)
+            if constexpr (MODE == 5)
               info = uniform_i(potrf_columns(Db, nb, po_m, lds));
             else
               info = uniform_i(potrf_small(Db, nb, po_m, lds));
@@ -3951,7 +3948,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
             }
           } else {
             if (part > 0) break;  // one workgroup factors the tile
-            info = uniform_i(potrf_tile_mixed<MODE == 5>(Dk, nb, tsz(tk), lds, by_columns));
+            info = uniform_i(potrf_tile_mixed<MODE == 5>(Dk, nb, tsz(tk), lds));
           }
         } else {
           const bool sub = unit >= 0;
@@ -4080,7 +4077,7 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
             double* const Cu = Dk + (int64_t)po_c * nb + po_r;
             const double* const Au = Dk + (int64_t)po_k * nb + po_r;
             const double* const Bu = Dk + (int64_t)po_k * nb + po_c;
-            gemm_reg64(Cu, Au, Bu, nb, M, N, K, lower, MODE == 5 && sn > PCOL_ORDER);
+            gemm_reg64(Cu, Au, Bu, nb, M, N, K, lower, MODE == 5);
             break;
           }
           // four rows per 16-byte lane: ld a multiple of 4 and three rows after the order

@@ -70,3 +70,10 @@ def test_wavefronts_agree_on_skipping():
     for at in re.finditer(r"ld_relaxed\(&a\.sinfo\[", text):
         guard = text[max(0, at.start() - 60):at.start()]
         assert re.search(r"if \((wave == 0|COMPACT)\) \{\s*[^{}]*$", guard), guard
+
+
+def test_no_kernel_is_chosen_by_a_fixed_order():
+    """A system's order is compared with nothing but sizes of its own: which
+    kernel runs follows from tile sizes, types and alignment."""
+    text = open(os.path.join(CSRC, "tchol_device.hip")).read()
+    assert re.findall(r"\bsn\s*[<>]=?\s*(?:\d+|[A-Z][A-Z_0-9]+)\b", text) == []
