@@ -855,7 +855,7 @@ std::shared_ptr<const Plan> get_run_merged_plan(int64_t n, int64_t nb, int32_t p
     });
   // the key's operation: with and without inverses
   return cached_run_plan(inv ? OP_FACTOR_INVT : TCHOL_OP_FACTOR, n, nb, policy, seed, [&]() -> std::shared_ptr<const Plan> {
-    if ((n + rt - 1) / rt > 1200) return nullptr;
+    if (n == 0 || (n + rt - 1) / rt > 1200) return nullptr;  // (nothing to do: nothing to run)
     auto plan = std::make_shared<Plan>();
     Plan& p = *plan;
     p.op = TCHOL_OP_BATCHED;
