@@ -84,6 +84,10 @@ struct Builder {
   static int32_t cdiv(int64_t a, int64_t b) { return (int32_t)((a + b - 1) / b); }
 };
 
+// Tiles per side that a plan may have, and the tasks of a system's merged DAG.
+constexpr int64_t kMaxTiles = 1200;
+int64_t batched_estimate(int64_t T) { return T * T * T / 6 + 3 * T * T + 4; }
+
 // ids of one system's tasks, for the edges between its factor and solve DAGs
 struct FactorIds {
   std::vector<int32_t> potrf, trsm;  // trsm[i * T + k]
@@ -159,6 +163,24 @@ int32_t potrf_parts(int64_t m) {
   return std::min<int32_t>(8, strips);
 }
 
+// The updates of tile (i, j), k = 0 .. j-1, are chained in k.  Every pair
+// (k, k+1) with k even that does not contain the last update (k+1 <= j-2)
+// is one GEMM2 task (K = 2 nb: half the loads and stores of the tile, and
+// half the work items' fixed costs, for the same products in the same
+// order); the last update before TRSM(i, j) stays a single GEMM, so the
+// critical path does not wait for a double update.  Run plans merge aligned
+// quadruples (k .. k+3, k % 4 == 0, k+3 <= j-2) the same way (GEMM4), and pairs
+// where no quadruple fits.  The last update of the task that applies update k:
+int32_t group_last(bool quads, int32_t j, int32_t k) {
+  if (quads && (k & ~3) + 3 <= j - 2) return (k & ~3) + 3;
+  return (k & ~1) + 1 <= j - 2 ? (k & ~1) + 1 : k;
+}
+// ... and the first.
+int32_t group_first(bool quads, int32_t j, int32_t k) {
+  if (quads && (k & ~3) + 3 <= j - 2) return k & ~3;
+  return (k & ~1) + 1 <= j - 2 ? k & ~1 : k;
+}
+
 // trtri: add TRTRI(k) after POTRF(k) (explicit inverses for the
 // mixed-precision solve; no task of the factorization waits for them).
 // inv_trsm: TRSM(i, k) applies L_kk^{-1} from TRTRI(k), which runs between
@@ -174,24 +196,9 @@ void build_factor(Builder& b, FactorIds* ids = nullptr, bool trtri = false, bool
   std::vector<int32_t> id_gemm((size_t)T * T * T, -1);
   auto ix2 = [T](int32_t i, int32_t k) { return (size_t)i * T + k; };
   auto ix3 = [T](int32_t i, int32_t j, int32_t k) { return ((size_t)k * T + i) * T + j; };
-  // The updates of tile (i, j), k = 0 .. j-1, are chained in k.  Every pair
-  // (k, k+1) with k even that does not contain the last update (k+1 <= j-2)
-  // is one GEMM2 task (K = 2 nb: half the loads and stores of the tile, and
-  // half the work items' fixed costs, for the same products in the same
-  // order); the last update before TRSM(i, j) stays a single GEMM, so the
-  // critical path does not wait for a double update.  id_gemm[(i, j, k)]
-  // holds the task that applies update k (a GEMM2 under both of its k).
-  // Run plans merge aligned quadruples (k .. k+3, k % 4 == 0, k+3 <= j-2) the
-  // same way (GEMM4), and pairs where no quadruple fits.
+  // id_gemm[(i, j, k)] holds the task that applies update k (a merged one under
+  // each of its k)
   const bool quads = b.p.quads;
-  auto group_last = [quads](int32_t j, int32_t k) {  // the last update of the task that applies update k
-    if (quads && (k & ~3) + 3 <= j - 2) return (k & ~3) + 3;
-    return (k & ~1) + 1 <= j - 2 ? (k & ~1) + 1 : k;
-  };
-  auto group_first = [quads](int32_t j, int32_t k) {
-    if (quads && (k & ~3) + 3 <= j - 2) return k & ~3;
-    return (k & ~1) + 1 <= j - 2 ? k & ~1 : k;
-  };
   auto gemm_parts = [&](int32_t i, int32_t j) {
     return Builder::cdiv(b.tile_size(i), b.s.gemm_m) * Builder::cdiv(b.tile_size(j), b.s.gemm_n);
   };
@@ -213,8 +220,8 @@ void build_factor(Builder& b, FactorIds* ids = nullptr, bool trtri = false, bool
       int32_t sb = Builder::cdiv(b.tile_size(i), b.s.syrk_b);
       id_syrk[ix2(i, k)] = b.add(TK_SYRK, i, i, k, sb * (sb + 1) / 2);
       for (int32_t j = k + 1; j < i; ++j) {
-        if (group_last(j, k) != k) continue;  // created with its last update, after TRSM(., k)
-        const int32_t k0 = group_first(j, k), len = k - k0 + 1;
+        if (group_last(quads, j, k) != k) continue;  // created with its last update, after TRSM(., k)
+        const int32_t k0 = group_first(quads, j, k), len = k - k0 + 1;
         const int32_t id = len > 1 ? b.add(len == 4 ? TK_GEMM4 : TK_GEMM2, i, j, k0, gemm_parts(i, j))
                                    : b.add(TK_GEMM, i, j, k, Builder::cdiv(b.tile_size(i), b.s.gemm1_m) *
                                                                  Builder::cdiv(b.tile_size(j), b.s.gemm1_n));
@@ -237,7 +244,7 @@ void build_factor(Builder& b, FactorIds* ids = nullptr, bool trtri = false, bool
       succ[id_syrk[ix2(i, k)]].push_back(k + 1 < i ? id_syrk[ix2(i, k + 1)] : id_potrf[i]);
       // each update task passes the tile on to the next one, the last to TRSM(i, j)
       for (int32_t j = k + 1; j < i; ++j) {
-        if (group_last(j, k) != k) continue;
+        if (group_last(quads, j, k) != k) continue;
         succ[id_gemm[ix3(i, j, k)]].push_back(k + 1 < j ? id_gemm[ix3(i, j, k + 1)] : id_trsm[ix2(i, j)]);
       }
     }
@@ -325,6 +332,93 @@ void build_solve(Builder& b, const FactorIds* after = nullptr, Diag diag = Diag:
       succ[id_bg[ix2(i, k)]].push_back(k - 1 > i ? id_bg[ix2(i, k - 1)] : id_bt[i]);
     }
   }
+}
+
+// The same tasks, edges and work items as build_factor's, counted.
+struct Counts {
+  int64_t task = 0, edge = 0, item = 0;
+  void add(int64_t tasks, int64_t parts) {
+    task += tasks;
+    item += tasks * parts;
+  }
+};
+
+void count_factor(Counts& c, int64_t n, int64_t nb, const Split& s, bool quads, bool finv, bool inv_trsm) {
+  const int32_t T = Builder::cdiv(n, nb);
+  auto ts = [&](int32_t i) { return std::min<int64_t>(nb, n - (int64_t)i * nb); };
+  for (int32_t k = 0; k < T; ++k) {
+    c.add(1, T > 1 ? potrf_parts(ts(k)) : 1);
+    c.edge += T - 1 - k;  // POTRF(k) or TRTRI(k) -> TRSM
+    if (inv_trsm && !finv && k + 1 < T) {
+      c.add(1, Builder::cdiv(ts(k), s.trsm_rows));
+      ++c.edge;
+    }
+  }
+  for (int32_t i = 1; i < T; ++i) {  // row i: TRSM and SYRK (i, k), k < i
+    const int64_t sb = Builder::cdiv(ts(i), s.syrk_b);
+    c.add(i, Builder::cdiv(ts(i), inv_trsm ? s.inv_rows : s.trsm_rows));
+    c.add(i, sb * (sb + 1) / 2);
+    // TRSM(i, k) -> SYRK(i, k), the updates of row i and of column i; SYRK's one
+    c.edge += (int64_t)i * (1 + T - 1 - i) + (int64_t)i * (i - 1) / 2 + i;
+  }
+  for (int32_t j = 1; j + 1 < T; ++j) {  // column j: the updates of tiles (i, j), i > j
+    int64_t single = 0, merged = 0;
+    for (int32_t k = 0; k < j;) {
+      const int32_t last = group_last(quads, j, k);
+      ++(last > k ? merged : single);
+      k = last + 1;
+    }
+    auto rows = [&](int64_t count, int64_t m) {
+      c.add(count * single, (int64_t)Builder::cdiv(m, s.gemm1_m) * Builder::cdiv(ts(j), s.gemm1_n));
+      c.add(count * merged, (int64_t)Builder::cdiv(m, s.gemm_m) * Builder::cdiv(ts(j), s.gemm_n));
+      c.edge += count * (single + merged);
+    };
+    rows(T - 2 - j, nb);
+    rows(1, ts(T - 1));
+  }
+}
+
+// As build_solve's, after a factorization of Tf tiles a side (0: alone), r of
+// them to a tile of this solve; inv: Diag::kInvHere; given: the factorization's
+// TRTRIs serve the solve.
+void count_solve(Counts& c, int64_t n, int64_t nb, const Split& s, int32_t Tf, int32_t r, bool inv, bool given) {
+  const int32_t T = Builder::cdiv(n, nb);
+  auto ts = [&](int32_t i) { return std::min<int64_t>(nb, n - (int64_t)i * nb); };
+  for (int32_t k = 0; k < T; ++k) {
+    const bool strips = inv && ts(k) % 16 == 0;
+    const int64_t gv = Builder::cdiv(ts(k), s.gemv_rows);
+    if (strips && !(given && k + 1 < T)) {
+      c.add(1, Builder::cdiv(ts(k), s.trsm_rows));
+      ++c.edge;
+    }
+    c.add(2, strips ? gv : 1);  // FTRSV, BTRSV
+    c.add(T - 1, gv);           // FGEMV(k, .), BGEMV(k, .): all that write row block k
+    if (Tf > 0) {
+      ++c.edge;  // from the factorization: the diagonal tile, then row k's others
+      c.edge += Tf == T ? k : (int64_t)k * r * (std::min(Tf, (k + 1) * r) - k * r);
+    }
+  }
+  c.edge += 4 * ((int64_t)T * (T - 1) / 2) + 1;
+}
+
+// What finalize refuses of them, and the result.
+bool size_from(const Counts& c, std::vector<System> systems, bool inv, PlanSize* out) {
+  if (c.edge > (int64_t)INT32_MAX || c.item > (int64_t)INT32_MAX / 2) return false;
+  for (auto& sy : systems) sy.T = sy.n == 0 ? 0 : Builder::cdiv(sy.n, sy.nb);
+  out->ntask = c.task;
+  out->nedge = c.edge;
+  out->nitem = c.item;
+  out->systems = std::move(systems);
+  out->inv = inv;
+  return true;
+}
+
+std::vector<System> one_system(int64_t n, int64_t nb) {
+  std::vector<System> v(1);
+  v[0].n = n;
+  v[0].nb = nb;
+  v[0].ld = n;
+  return v;
 }
 
 // Adjoint of the factorization: the reverse of the factor DAG, steps k
@@ -668,7 +762,7 @@ std::shared_ptr<Plan> build_plan(int32_t op, int64_t n, int64_t nb, int32_t poli
   p.finv = run && op == OP_FACTOR_INVT;
   int64_t T64 = n == 0 ? 0 : (n + nb - 1) / nb;
   // the factorization's DAG has about T^3/6 tasks, the adjoint's T^3/3
-  if (T64 > 1200 || (op == TCHOL_OP_BACKWARD && T64 > 160)) return nullptr;
+  if (T64 > kMaxTiles || (op == TCHOL_OP_BACKWARD && T64 > 160)) return nullptr;
   p.T = (int32_t)T64;
   System sy;
   sy.n = n;
@@ -718,9 +812,9 @@ std::shared_ptr<Plan> build_batched_plan(const std::vector<System>& systems, int
   int64_t est = 0;
   for (auto& sy : p.systems) {
     const int64_t T64 = sy.n == 0 ? 0 : (sy.n + sy.nb - 1) / sy.nb;
-    if (T64 > 1200) return nullptr;
+    if (T64 > kMaxTiles) return nullptr;
     sy.T = (int32_t)T64;
-    est += T64 * T64 * T64 / 6 + 3 * T64 * T64 + 4;
+    est += batched_estimate(T64);
   }
   if (est > (int64_t)INT32_MAX / 4) return nullptr;
   std::vector<std::vector<int32_t>> succ;
@@ -814,22 +908,40 @@ const Split& run_split(int32_t op, int64_t nb) {
   return nb <= kRunTile && (op == TCHOL_OP_FACTOR || op == OP_FACTOR_INVT || op == TCHOL_OP_BATCHED) ? fine : split_for(op);
 }
 
-// The run plans, a small process-wide cache.
+// Bytes that a plan keeps.
+int64_t plan_bytes(const Plan& p) { return 44 * p.ntask() + 4 * p.nedge() + 8 * p.nitem(); }
+
+// The run plans, a small process-wide cache: at most 32, and 1 GiB of them
+// besides the newest.
+struct RunPlans {
+  std::mutex mu;
+  std::map<std::tuple<bool, int32_t, int64_t, int64_t, int32_t, uint32_t>, std::shared_ptr<const Plan>> cache;
+  int64_t bytes = 0;
+};
+
+RunPlans& run_plans() {
+  static RunPlans r;
+  return r;
+}
+
 template <class Make>
-std::shared_ptr<const Plan> cached_run_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed, Make make) {
-  static std::mutex mu;
-  static std::map<std::tuple<int32_t, int64_t, int64_t, int32_t, uint32_t>, std::shared_ptr<const Plan>> cache;
-  auto key = std::make_tuple(op, n, nb, policy, policy == TCHOL_POLICY_RANDOM ? seed : 0u);
+std::shared_ptr<const Plan> cached_run_plan(bool merged, int32_t op, int64_t n, int64_t nb, int32_t policy,
+                                            uint32_t seed, Make make) {
+  RunPlans& shared = run_plans();
+  const auto key = std::make_tuple(merged, op, n, nb, policy, policy == TCHOL_POLICY_RANDOM ? seed : 0u);
   {
-    std::lock_guard<std::mutex> g(mu);
-    auto it = cache.find(key);
-    if (it != cache.end()) return it->second;
+    std::lock_guard<std::mutex> g(shared.mu);
+    auto it = shared.cache.find(key);
+    if (it != shared.cache.end()) return it->second;
   }
   std::shared_ptr<const Plan> p = make();
   if (!p) return nullptr;
-  std::lock_guard<std::mutex> g(mu);
-  if (cache.size() > 32) cache.clear();
-  cache[key] = p;
+  std::lock_guard<std::mutex> g(shared.mu);
+  if (shared.cache.size() >= 32 || shared.bytes > ((int64_t)1 << 30)) {
+    shared.cache.clear();
+    shared.bytes = 0;
+  }
+  if (shared.cache.emplace(key, p).second) shared.bytes += plan_bytes(*p);
   return p;
 }
 
@@ -838,7 +950,7 @@ std::shared_ptr<const Plan> cached_run_plan(int32_t op, int64_t n, int64_t nb, i
 std::shared_ptr<const Plan> get_run_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed) {
   if (op != TCHOL_OP_FACTOR && op != OP_FACTOR_INVT) return get_plan(op, n, nb, policy, seed);
   const int64_t rt = run_tile(n, nb);
-  return cached_run_plan(op, n, rt, policy, seed, [&]() -> std::shared_ptr<const Plan> {
+  return cached_run_plan(false, op, n, rt, policy, seed, [&]() -> std::shared_ptr<const Plan> {
     return build_plan(op, n, rt, policy, seed, run_split(op, rt), rt <= kRunTile, true);
   });
 }
@@ -850,12 +962,12 @@ std::shared_ptr<const Plan> get_run_merged_plan(int64_t n, int64_t nb, int32_t p
   systems[0].nb = rt;
   systems[0].ld = n;
   if (rt > kRunTile)
-    return cached_run_plan(inv ? OP_FACTOR_INVT : TCHOL_OP_FACTOR, n, nb, policy, seed, [&]() -> std::shared_ptr<const Plan> {
+    return cached_run_plan(true, inv ? OP_FACTOR_INVT : TCHOL_OP_FACTOR, n, nb, policy, seed, [&]() -> std::shared_ptr<const Plan> {
       return build_batched_plan(systems, policy, seed, default_split(), inv, true);
     });
   // the key's operation: with and without inverses
-  return cached_run_plan(inv ? OP_FACTOR_INVT : TCHOL_OP_FACTOR, n, nb, policy, seed, [&]() -> std::shared_ptr<const Plan> {
-    if (n == 0 || (n + rt - 1) / rt > 1200) return nullptr;  // (nothing to do: nothing to run)
+  return cached_run_plan(true, inv ? OP_FACTOR_INVT : TCHOL_OP_FACTOR, n, nb, policy, seed, [&]() -> std::shared_ptr<const Plan> {
+    if (n == 0 || (n + rt - 1) / rt > kMaxTiles) return nullptr;  // (nothing to do: nothing to run)
     auto plan = std::make_shared<Plan>();
     Plan& p = *plan;
     p.op = TCHOL_OP_BATCHED;
@@ -881,6 +993,66 @@ std::shared_ptr<const Plan> get_run_merged_plan(int64_t n, int64_t nb, int32_t p
     if (!finalize(p, succ, policy, seed)) return nullptr;
     return plan;
   });
+}
+
+PlanSize size_of(const Plan& p) {
+  PlanSize z;
+  z.ntask = p.ntask();
+  z.nedge = p.nedge();
+  z.nitem = p.nitem();
+  z.systems = p.systems;
+  z.inv = p.inv;
+  return z;
+}
+
+bool factor_size(int32_t op, int64_t n, int64_t nb, PlanSize* out) {
+  Counts c;
+  const int64_t T64 = n == 0 ? 0 : (n + nb - 1) / nb;
+  if (T64 > kMaxTiles) return false;
+  if (n > 0) count_factor(c, n, nb, split_for(op), false, false, op == OP_FACTOR_INVT);
+  // (an empty plan applies nothing)
+  return size_from(c, one_system(n, nb), n > 0 && op == OP_FACTOR_INVT, out);
+}
+
+bool run_factor_size(int32_t op, int64_t n, int64_t nb, PlanSize* out) {
+  const int64_t rt = run_tile(n, nb);
+  Counts c;
+  if (n == 0 || (n + rt - 1) / rt > kMaxTiles) return false;
+  const bool inv = op == OP_FACTOR_INVT;
+  count_factor(c, n, rt, run_split(op, rt), true, inv && rt <= kRunTile, inv);
+  return size_from(c, one_system(n, rt), inv, out);
+}
+
+bool merged_size(int64_t n, int64_t nb, bool inv, PlanSize* out) {
+  Counts c;
+  const int64_t T64 = n == 0 ? 0 : (n + nb - 1) / nb;
+  if (T64 > kMaxTiles || batched_estimate(T64) > (int64_t)INT32_MAX / 4) return false;
+  if (n > 0) {
+    count_factor(c, n, nb, default_split(), false, false, inv);
+    count_solve(c, n, nb, default_split(), (int32_t)T64, 1, inv, inv);
+  }
+  return size_from(c, one_system(n, nb), inv, out);
+}
+
+bool run_merged_size(int64_t n, int64_t nb, bool inv, PlanSize* out) {
+  const int64_t rt = run_tile(n, nb), T64 = (n + rt - 1) / rt;
+  if (n == 0 || T64 > kMaxTiles) return false;
+  Counts c;
+  std::vector<System> systems = one_system(n, rt);
+  if (rt > kRunTile) {
+    if (batched_estimate(T64) > (int64_t)INT32_MAX / 4) return false;
+    count_factor(c, n, rt, default_split(), true, false, inv);
+    count_solve(c, n, rt, default_split(), (int32_t)T64, 1, inv, inv);
+  } else {
+    const Split& s = run_split(TCHOL_OP_BATCHED, rt);
+    count_factor(c, n, rt, s, true, inv, inv);
+    count_solve(c, n, nb, s, (int32_t)T64, (int32_t)(nb / rt), inv, false);
+    if (nb != rt) {
+      systems.push_back(systems[0]);
+      systems[1].nb = nb;
+    }
+  }
+  return size_from(c, std::move(systems), inv, out);
 }
 
 }  // namespace tchol

@@ -84,6 +84,26 @@ constexpr int32_t OP_SOLVE_SUBST = 18;
 // the factorization of the merged factor + solve launch, alone.
 constexpr int32_t OP_FACTOR_INVT = 19;
 
+// What the size of a launch's workspace depends on: a plan's numbers of tasks,
+// edges and work items, its systems' orders and tile sizes, and whether it
+// applies inverses.
+struct PlanSize {
+  int64_t ntask = 0, nedge = 0, nitem = 0;
+  std::vector<System> systems;
+  bool inv = false;
+};
+
+PlanSize size_of(const Plan& p);
+
+// The sizes of the plans that get_plan (TCHOL_OP_FACTOR and OP_FACTOR_INVT),
+// get_batched_plan (one system), get_run_plan and get_run_merged_plan (below)
+// give, for any policy, without building them: O(T^2) steps where a plan has
+// about T^3 / 6 tasks.  False where those return nullptr.
+bool factor_size(int32_t op, int64_t n, int64_t nb, PlanSize* out);
+bool merged_size(int64_t n, int64_t nb, bool inv, PlanSize* out);
+bool run_factor_size(int32_t op, int64_t n, int64_t nb, PlanSize* out);
+bool run_merged_size(int64_t n, int64_t nb, bool inv, PlanSize* out);
+
 // Builds (or fetches from a process-wide cache) the plan.  Returns nullptr
 // for arguments the planner cannot represent (task counts beyond int32).
 std::shared_ptr<const Plan> get_plan(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed);

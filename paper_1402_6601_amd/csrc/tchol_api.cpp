@@ -52,16 +52,18 @@ struct Layout {
   int64_t npool = 0;  // words of the POTRF pools
 };
 
+using tchol::PlanSize;
+
 // Diagonal tiles over all systems of a plan (one POTRF pool each).
-int64_t diag_tiles(const Plan& p) {
+int64_t diag_tiles(const PlanSize& p) {
   int64_t t = 0;
   for (const auto& sy : p.systems) t += sy.n == 0 ? 0 : (sy.n + sy.nb - 1) / sy.nb;
   return t;
 }
 
-Layout layout_of(const Plan& p) {
+Layout layout_of(const PlanSize& p) {
   Layout L;
-  const int64_t nt = p.ntask(), ns = (int64_t)p.systems.size();
+  const int64_t nt = p.ntask, ns = (int64_t)p.systems.size();
   L.npool = POOL_WORDS * diag_tiles(p);
   L.hdr = 0;
   L.dep = align_up(HDR_WORDS * 4);
@@ -71,11 +73,12 @@ Layout layout_of(const Plan& p) {
   L.dep0 = align_up(L.pool + 4 * L.npool);
   L.desc = align_up(L.dep0 + 4 * nt);
   L.succ = align_up(L.desc + 4 * DESC_WORDS * nt);
-  L.items = align_up(L.succ + 4 * p.nedge());
-  L.sys = align_up(L.items + 8 * p.nitem());
+  L.items = align_up(L.succ + 4 * p.nedge);
+  L.sys = align_up(L.items + 8 * p.nitem);
   L.end = align_up(L.sys + 8 * SYS_WORDS * ns);
   return L;
 }
+Layout layout_of(const Plan& p) { return layout_of(tchol::size_of(p)); }
 
 // The FP64 solve's explicit inverses and intermediate vector (plans with
 // inv), after the scheduler's regions: L_kk^{-T} of every diagonal tile
@@ -84,7 +87,7 @@ struct InvLayout {
   int64_t dinvt = 0, dinv = 0, sx = 0, end = 0;
 };
 
-InvLayout inv_layout(const Plan& p, int64_t nrhs) {
+InvLayout inv_layout(const PlanSize& p, int64_t nrhs) {
   InvLayout V;
   V.end = layout_of(p).end;
   if (!p.inv || p.systems.empty()) return V;
@@ -97,6 +100,7 @@ InvLayout inv_layout(const Plan& p, int64_t nrhs) {
   V.end = align_up(V.sx + 8 * sy.n * std::max<int64_t>(nrhs, 1));
   return V;
 }
+InvLayout inv_layout(const Plan& p, int64_t nrhs) { return inv_layout(tchol::size_of(p), nrhs); }
 
 // The constant part of the workspace for one plan, in pinned host memory
 // when the runtime can provide it.
@@ -395,13 +399,15 @@ int32_t run(int32_t op, double* A, double* B, int64_t n, int64_t nb, int64_t nrh
                      : op == TCHOL_OP_FACTOR && o.inv_trsm ? tchol::OP_FACTOR_INVT
                                                            : op;
   // a traced launch runs the plan that the queries describe, and so does one
-  // whose workspace does not hold the run plan
-  auto plan = tchol::get_plan(pop, n, nb, o.policy, o.seed);
-  if (!plan) return TCHOL_E_UNSUPPORTED;
-  if (!o.trace) {
-    auto rp = tchol::get_run_plan(pop, n, nb, o.policy, o.seed);
-    if (rp && ws_bytes >= inv_layout(*rp, nrhs).end) plan = rp;
+  // whose workspace holds that plan but not the run plan
+  std::shared_ptr<const Plan> plan;
+  if (op == TCHOL_OP_FACTOR && !o.trace) {
+    PlanSize r;
+    if (tchol::run_factor_size(pop, n, nb, &r) && ws_bytes >= inv_layout(r, nrhs).end)
+      plan = tchol::get_run_plan(pop, n, nb, o.policy, o.seed);
   }
+  if (!plan) plan = tchol::get_plan(pop, n, nb, o.policy, o.seed);
+  if (!plan) return TCHOL_E_UNSUPPORTED;
   if (o.trace && o.trace_words / 4 < plan->nitem()) return -(ws_arg + 3);
   auto img = image_of(plan);
   // 16-byte panel transfers need an even leading dimension and an aligned matrix
@@ -571,19 +577,14 @@ namespace tchol {
 
 // Workspace bytes of the merged factor + solve launch (inv as below).
 int64_t factor_solve_bytes(int64_t n, int64_t nb, int64_t nrhs, bool inv) {
-  std::vector<tchol::System> systems(1);
-  systems[0].n = n;
-  systems[0].nb = nb;
-  auto plan = tchol::get_batched_plan(systems, TCHOL_POLICY_RANK, 0, inv);
-  if (!plan) return TCHOL_E_UNSUPPORTED;
-  // every policy yields the same task, edge and item counts, hence the same layout
-  return inv_layout(*plan, nrhs).end;
+  PlanSize q;
+  return tchol::merged_size(n, nb, inv, &q) ? inv_layout(q, nrhs).end : (int64_t)TCHOL_E_UNSUPPORTED;
 }
 
 // The same for the plan that the launch runs when its workspace holds it.
-int64_t factor_solve_run_bytes(int64_t n, int64_t nb, int64_t nrhs) {
-  auto plan = tchol::get_run_merged_plan(n, nb, TCHOL_POLICY_LIST, 0, true);
-  return plan ? inv_layout(*plan, nrhs).end : 0;
+int64_t factor_solve_run_bytes(int64_t n, int64_t nb, int64_t nrhs, bool inv) {
+  PlanSize r;
+  return tchol::run_merged_size(n, nb, inv, &r) ? inv_layout(r, nrhs).end : 0;
 }
 
 // The merged factor + solve launch on validated arguments (n > 0).  pinned:
@@ -602,11 +603,11 @@ int32_t factor_solve_run(double* A, int64_t n, int64_t nb, double* B, int64_t nr
   systems[0].nb = nb;
   systems[0].ld = n;
   // a traced launch runs the plan that the queries describe, and so does one
-  // whose workspace does not hold the run plan
+  // whose workspace holds that plan but not the run plan
   std::shared_ptr<const Plan> plan;
   if (!o.trace) {
-    plan = tchol::get_run_merged_plan(n, nb, o.policy, o.seed, inv);
-    if (plan && ws_bytes < inv_layout(*plan, nrhs).end) plan = nullptr;
+    const int64_t run_need = factor_solve_run_bytes(n, nb, nrhs, inv);
+    if (run_need > 0 && ws_bytes >= run_need) plan = tchol::get_run_merged_plan(n, nb, o.policy, o.seed, inv);
   }
   if (!plan) plan = tchol::get_batched_plan(systems, o.policy, o.seed, inv);
   if (!plan) return TCHOL_E_UNSUPPORTED;
@@ -653,22 +654,22 @@ int64_t tchol_workspace_bytes(int32_t op, int64_t n, int64_t nb, int64_t nrhs) {
   if (n < 0) return -2;
   if (!nb_ok(nb)) return -3;
   if (op == TCHOL_OP_SOLVE && nrhs < 0) return -4;
-  // the factorization's workspace covers opts.inv_trsm (its DAG and inverses)
-  auto plan = tchol::get_plan(op == TCHOL_OP_FACTOR ? tchol::OP_FACTOR_INVT : op, n, nb, TCHOL_POLICY_RANK, 0);
+  if (op == TCHOL_OP_FACTOR) {
+    // covers opts.inv_trsm (its DAG and inverses) and the plans that launches run
+    int64_t end = 0;
+    for (int32_t pop : {tchol::OP_FACTOR_INVT, (int32_t)TCHOL_OP_FACTOR}) {
+      PlanSize q, r;
+      if (!tchol::factor_size(pop, n, nb, &q)) return TCHOL_E_UNSUPPORTED;
+      end = std::max(end, inv_layout(q, nrhs).end);
+      if (tchol::run_factor_size(pop, n, nb, &r)) end = std::max(end, inv_layout(r, nrhs).end);
+    }
+    return end;
+  }
+  auto plan = tchol::get_plan(op, n, nb, TCHOL_POLICY_RANK, 0);
   if (!plan) return TCHOL_E_UNSUPPORTED;
   if (op == TCHOL_OP_BACKWARD) return back_layout(n, nb, *plan).end;
   // every policy yields the same task, edge and item counts, hence the same layout
-  int64_t end = inv_layout(*plan, nrhs).end;
-  if (op == TCHOL_OP_FACTOR) {
-    auto plain = tchol::get_plan(TCHOL_OP_FACTOR, n, nb, TCHOL_POLICY_RANK, 0);
-    if (!plain) return TCHOL_E_UNSUPPORTED;
-    end = std::max(end, inv_layout(*plain, nrhs).end);
-    for (int32_t rop : {tchol::OP_FACTOR_INVT, (int32_t)TCHOL_OP_FACTOR}) {
-      auto rp = tchol::get_run_plan(rop, n, nb, TCHOL_POLICY_LIST, 0);
-      if (rp) end = std::max(end, inv_layout(*rp, nrhs).end);
-    }
-  }
-  return end;
+  return inv_layout(*plan, nrhs).end;
 }
 
 int32_t tchol_factor_ex(double* A, int64_t n, int64_t nb, void* ws, int64_t ws_bytes, void* stream,
@@ -744,7 +745,7 @@ int64_t tchol_factor_solve_workspace_bytes(int64_t n, int64_t nb, int64_t nrhs) 
   const int64_t need = tchol::factor_solve_bytes(n, nb, nrhs, true);
   if (need < 0) return need;
   // the inverses (n nb doubles) make the substituting launch's plans the smaller ones
-  return std::max(need, tchol::factor_solve_run_bytes(n, nb, nrhs));
+  return std::max(need, tchol::factor_solve_run_bytes(n, nb, nrhs, true));
 }
 
 int32_t tchol_factor_solve(double* A, int64_t n, int64_t nb, double* B, int64_t nrhs, void* ws, int64_t ws_bytes,

@@ -1,0 +1,30 @@
+"""Workspace queries count the sizes of the plans without building them: equal
+to the built plans' over orders, tile sizes, inverses and both kinds of plan,
+and cheap for small tiles of large orders
+(host only, the device entry points are stubs)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1402_6601_amd", "csrc")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_sizes_and_cost_of_the_queries(tmp_path):
+    exe = str(tmp_path / "plan_size_host")
+    cmd = ["g++", "-std=c++17", "-O2", "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(ROCM, "include"),
+           "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
+           os.path.join(ROOT, "tests", "plan_size_host.cpp"), os.path.join(CSRC, "plan.cpp"),
+           os.path.join(CSRC, "tchol_api.cpp"), "-L" + os.path.join(ROCM, "lib"), "-lamdhip64",
+           "-Wl,-rpath," + os.path.join(ROCM, "lib"), "-o", exe]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0 and not os.path.exists(os.path.join(ROCM, "include", "hip", "hip_runtime.h")):
+        pytest.skip("ROCm headers not available")
+    assert r.returncode == 0, r.stdout[-4000:]
+    r = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-4000:]
+    assert r.stdout.rstrip().endswith("; 0 failures")
