@@ -402,7 +402,9 @@ int32_t run(int32_t op, double* A, double* B, int64_t n, int64_t nb, int64_t nrh
   // whose workspace holds that plan but not the run plan
   std::shared_ptr<const Plan> plan;
   if (op == TCHOL_OP_FACTOR && !o.trace) {
-    PlanSize r;
+    PlanSize q, r;
+    if (!tchol::factor_size(pop, n, nb, &q)) return TCHOL_E_UNSUPPORTED;
+    if (ws_bytes < inv_layout(q, nrhs).end) return -(ws_arg + 1);
     if (tchol::run_factor_size(pop, n, nb, &r) && ws_bytes >= inv_layout(r, nrhs).end)
       plan = tchol::get_run_plan(pop, n, nb, o.policy, o.seed);
   }
@@ -606,6 +608,9 @@ int32_t factor_solve_run(double* A, int64_t n, int64_t nb, double* B, int64_t nr
   // whose workspace holds that plan but not the run plan
   std::shared_ptr<const Plan> plan;
   if (!o.trace) {
+    const int64_t need = factor_solve_bytes(n, nb, nrhs, inv);
+    if (need < 0) return (int32_t)need;
+    if (ws_bytes < need) return -7;
     const int64_t run_need = factor_solve_run_bytes(n, nb, nrhs, inv);
     if (run_need > 0 && ws_bytes >= run_need) plan = tchol::get_run_merged_plan(n, nb, o.policy, o.seed, inv);
   }

@@ -90,6 +90,19 @@ int main() {
   CHECK(tchol_workspace_bytes(TCHOL_OP_FACTOR, 0, 128, 0) > 0);
   std::printf("plan sizes: %d failures\n", failures);
 
+  // a workspace below what the queried plan needs stays refused, also where the
+  // run plan would fit (order 16384 by tiles of 512: its merged updates save room)
+  double* fake = reinterpret_cast<double*>(0x10000);
+  const int32_t n1 = 16384, nb1 = 512;
+  const int64_t need = tchol_batched_workspace_bytes(&n1, &nb1, 1);
+  CHECK(tchol::run_merged_size(n1, nb1, false, &z));
+  tchol::PlanSize q;
+  CHECK(tchol::merged_size(n1, nb1, false, &q) && z.ntask < q.ntask && z.nedge < q.nedge && z.nitem < q.nitem);
+  tchol_opts subst = {};
+  subst.subst = 1;
+  CHECK(tchol_factor_solve(fake, n1, nb1, fake, 1, fake, need - 256, nullptr, &subst) == -7);
+  CHECK(tchol_factor(fake, n1, nb1, fake, 1 << 18, nullptr) == -5);
+
   // queries build no plan: small tiles of large orders would take seconds and gigabytes
   rusage before, after;
   getrusage(RUSAGE_SELF, &before);

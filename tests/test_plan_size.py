@@ -1,6 +1,6 @@
 """Workspace queries count the sizes of the plans without building them: equal
 to the built plans' over orders, tile sizes, inverses and both kinds of plan,
-and cheap for small tiles of large orders
+cheap for small tiles of large orders, and with the refusals they always had
 (host only, the device entry points are stubs)."""
 import os
 import shutil
