@@ -1,8 +1,13 @@
 """The plans that ordinary launches run, and what they are asked for on the host (no GPU)."""
+import os
+import shutil
 import subprocess
 import sys
 
 import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1402_6601_amd", "csrc")
 
 tc = pytest.importorskip("paper_1402_6601_amd")
 
@@ -21,3 +26,30 @@ def test_workspace_of_an_empty_system(nb):
     assert r.returncode == 0, (r.returncode, r.stderr[-500:])
     both, factor = map(int, r.stdout.split())
     assert 0 < factor <= both < 1 << 20
+
+
+@pytest.fixture(scope="module")
+def checker(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++")
+    exe = str(tmp_path_factory.mktemp("run_plans") / "run_plan_host")
+    cmd = ["g++", "-std=c++17", "-O2", "-Wall", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
+           os.path.join(ROOT, "tests", "run_plan_host.cpp"), os.path.join(CSRC, "plan.cpp"), "-o", exe]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-4000:]
+    return exe
+
+
+def test_data_flow_claim_order_and_items(checker):
+    """Two tile sizes in one plan, merged updates, POTRF with its inverse, fine
+    work items: conflicts ordered, claim orders topological, outputs covered."""
+    r = subprocess.run([checker], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-4000:]
+    assert r.stdout.rstrip().endswith(", 0 failures")
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2, 3, 4, 5, 6, 7, 12, 19])
+def test_the_check_notices_missing_edges(checker, kind):
+    """Without the edges into one kind of task the check must fail."""
+    r = subprocess.run([checker, str(kind)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert r.returncode == 1 and "not ordered" in r.stdout
