@@ -62,6 +62,11 @@ extern "C" {
 #define TCHOL_POLICY_RANK 1   /* decreasing upward rank (task by task)      */
 #define TCHOL_POLICY_FIFO 2   /* step-major: (k, kind, i, j) ascending      */
 #define TCHOL_POLICY_RANDOM 3 /* a seeded random topological order          */
+#define TCHOL_PLAN_RUN 0x100  /* added to a policy, for the operations TCHOL_OP_FACTOR
+                                 and TCHOL_OP_FACTOR_SOLVE: tchol_plan_query describes,
+                                 and a traced tchol_factor_ex or tchol_factor_solve
+                                 runs, the plan that an untraced launch runs in a
+                                 workspace of the queried size                 */
 
 #define TCHOL_E_HIP (-100)         /* a HIP runtime call failed              */
 #define TCHOL_E_TIMEOUT (-101)     /* the kernel's bounded wait expired      */
@@ -95,8 +100,10 @@ typedef struct tchol_opts {
                           = 0); for tchol_solve_mixed, TCHOL_OP_MIXED_FACTOR), or NULL:
                           {claim, start} and {end} wall clock (100 MHz),
                           {task, part | wg<<32}.  A traced launch runs the plan
-                          that the query describes; without a trace a factorization
-                          may run at smaller tiles than nb                       */
+                          that the query with the same policy describes: without
+                          TCHOL_PLAN_RUN the one at nb, where an untraced
+                          factorization may run at smaller tiles and merge more
+                          updates (same accuracy, other rounding)                */
   int64_t trace_words; /* length of trace in uint64 words; with trace set, a call
                           whose launch has more than trace_words / 4 work items
                           returns -i for its opts argument i and launches nothing */
@@ -344,7 +351,10 @@ TCHOL_API const char *tchol_strerror(int32_t code);
    work items item_task / item_part (nitem).  The plan is the one at the given
    nb, which a traced launch runs; an untraced factorization whose workspace
    (of the size tchol_workspace_bytes or tchol_factor_solve_workspace_bytes
-   gives) holds it may run at smaller tiles, with a shorter critical path.
+   gives) holds it may run at smaller tiles, with a shorter critical path.  With
+   TCHOL_PLAN_RUN added to the policy the plan is that one: its factorization's
+   tiles are as many a side as it has POTRF tasks, its solve's (FTRSV, FGEMV,
+   BTRSV, BGEMV and, where they differ, TRTRI) are at nb.
    Returns 0 or a negative code. */
 TCHOL_API int32_t tchol_plan_query(int32_t op, int64_t n, int64_t nb, int32_t policy, uint32_t seed, int64_t *counts,
                          int32_t *kind, int32_t *ti, int32_t *tj, int32_t *tk, int32_t *parts,

@@ -24,12 +24,15 @@ LIB_PATH = os.path.join(_HERE, "libtchol.so")
 
 OP_FACTOR, OP_SOLVE, OP_BATCHED, OP_BACKWARD, OP_MIXED_FACTOR, OP_FACTOR_SOLVE = 0, 1, 2, 3, 4, 5
 POLICY_LIST, POLICY_RANK, POLICY_FIFO, POLICY_RANDOM = 0, 1, 2, 3
+#: Added to a policy: plan_query describes, and a traced factor_ or
+#: factor_solve_ runs, the plan of an untraced launch (TCHOL_PLAN_RUN).
+PLAN_RUN = 0x100
 E_HIP, E_TIMEOUT, E_UNSUPPORTED, E_INTERNAL, E_NOCONV, E_SCRATCH = -100, -101, -102, -103, -104, -105
 NOALLOC_SCRATCH_BYTES = 16 << 20
 LOWP_FP32, LOWP_BF16 = 1, 2
 KIND_NAMES = ["POTRF", "TRSM", "SYRK", "GEMM", "FTRSV", "FGEMV", "BTRSV", "BGEMV", "GREV", "TREV", "DPART", "PREV",
               "TRTRI", "DRED", "GEMM2", "PADJM", "PADJY", "PADJS",
-              "GREV2"]
+              "GREV2", "GEMM4"]
 
 _lib = None
 
@@ -136,7 +139,9 @@ def factor_solve_workspace_bytes(n: int, nb: int, nrhs: int) -> int:
 # ---------------------------------------------------------------- plan introspection (host only)
 
 def plan_query(op: int, n: int, nb: int, policy: int = POLICY_LIST, seed: int = 0) -> dict:
-    """The task DAG, ranks and claim order the library would execute (no GPU needed)."""
+    """The task DAG, ranks and claim order of a launch (no GPU needed): the plan
+    at nb, which a traced launch runs; with PLAN_RUN added to the policy the
+    one that an untraced factorization runs."""
     lib = load()
     counts = np.zeros(4, dtype=np.int64)
     P32 = ctypes.POINTER(ctypes.c_int32)

@@ -275,6 +275,9 @@ hipError_t device_info(DeviceInfo* out) {
 }
 
 bool policy_ok(int32_t p) { return p >= TCHOL_POLICY_LIST && p <= TCHOL_POLICY_RANDOM; }
+// A policy to which TCHOL_PLAN_RUN may have been added (not a negative number, in which every bit may be set).
+bool run_policy(int32_t p) { return p >= 0 && (p & TCHOL_PLAN_RUN) != 0; }
+int32_t claim_policy(int32_t p) { return run_policy(p) ? p & ~TCHOL_PLAN_RUN : p; }
 
 bool nb_ok(int64_t nb) { return nb >= TCHOL_NB_MIN && nb <= TCHOL_NB_MAX && nb % 16 == 0; }
 
@@ -394,21 +397,22 @@ int32_t execute(const Plan& plan, const Image& img, double* A, double* B, int64_
 int32_t run(int32_t op, double* A, double* B, int64_t n, int64_t nb, int64_t nrhs, void* ws, int64_t ws_bytes,
             void* stream_v, const tchol_opts* opts, int32_t ws_arg) {
   const tchol_opts& o = opts ? *opts : kDefaultOpts;
-  if (!policy_ok(o.policy)) return TCHOL_E_UNSUPPORTED;
+  const int32_t policy = op == TCHOL_OP_FACTOR ? claim_policy(o.policy) : o.policy;
+  if (!policy_ok(policy)) return TCHOL_E_UNSUPPORTED;
   const int32_t pop = op == TCHOL_OP_SOLVE && o.subst        ? tchol::OP_SOLVE_SUBST
                      : op == TCHOL_OP_FACTOR && o.inv_trsm ? tchol::OP_FACTOR_INVT
                                                            : op;
-  // a traced launch runs the plan that the queries describe, and so does one
-  // whose workspace holds that plan but not the run plan
+  // a traced launch runs the plan that the query with its policy describes; one
+  // whose workspace holds the queried plan but not the run plan runs the former
   std::shared_ptr<const Plan> plan;
-  if (op == TCHOL_OP_FACTOR && !o.trace) {
+  if (op == TCHOL_OP_FACTOR && (!o.trace || run_policy(o.policy))) {
     PlanSize q, r;
     if (!tchol::factor_size(pop, n, nb, &q)) return TCHOL_E_UNSUPPORTED;
     if (ws_bytes < inv_layout(q, nrhs).end) return -(ws_arg + 1);
     if (tchol::run_factor_size(pop, n, nb, &r) && ws_bytes >= inv_layout(r, nrhs).end)
-      plan = tchol::get_run_plan(pop, n, nb, o.policy, o.seed);
+      plan = tchol::get_run_plan(pop, n, nb, policy, o.seed);
   }
-  if (!plan) plan = tchol::get_plan(pop, n, nb, o.policy, o.seed);
+  if (!plan) plan = tchol::get_plan(pop, n, nb, policy, o.seed);
   if (!plan) return TCHOL_E_UNSUPPORTED;
   if (o.trace && o.trace_words / 4 < plan->nitem()) return -(ws_arg + 3);
   auto img = image_of(plan);
@@ -598,23 +602,24 @@ int64_t factor_solve_run_bytes(int64_t n, int64_t nb, int64_t nrhs, bool inv) {
 int32_t factor_solve_run(double* A, int64_t n, int64_t nb, double* B, int64_t nrhs, void* ws, int64_t ws_bytes,
                          void* stream, const tchol_opts* opts, bool pinned, bool inv) {
   const tchol_opts& o = opts ? *opts : kDefaultOpts;
-  if (!policy_ok(o.policy)) return TCHOL_E_UNSUPPORTED;
+  const int32_t policy = claim_policy(o.policy);
+  if (!policy_ok(policy)) return TCHOL_E_UNSUPPORTED;
   // one system of the merged factor + solve DAG: A at offset 0 with ld n, B at 0
   std::vector<tchol::System> systems(1);
   systems[0].n = n;
   systems[0].nb = nb;
   systems[0].ld = n;
-  // a traced launch runs the plan that the queries describe, and so does one
-  // whose workspace holds that plan but not the run plan
+  // a traced launch runs the plan that the query with its policy describes; one
+  // whose workspace holds the queried plan but not the run plan runs the former
   std::shared_ptr<const Plan> plan;
-  if (!o.trace) {
+  if (!o.trace || run_policy(o.policy)) {
     const int64_t need = factor_solve_bytes(n, nb, nrhs, inv);
     if (need < 0) return (int32_t)need;
     if (ws_bytes < need) return -7;
     const int64_t run_need = factor_solve_run_bytes(n, nb, nrhs, inv);
-    if (run_need > 0 && ws_bytes >= run_need) plan = tchol::get_run_merged_plan(n, nb, o.policy, o.seed, inv);
+    if (run_need > 0 && ws_bytes >= run_need) plan = tchol::get_run_merged_plan(n, nb, policy, o.seed, inv);
   }
-  if (!plan) plan = tchol::get_batched_plan(systems, o.policy, o.seed, inv);
+  if (!plan) plan = tchol::get_batched_plan(systems, policy, o.seed, inv);
   if (!plan) return TCHOL_E_UNSUPPORTED;
   const InvLayout V = inv_layout(*plan, nrhs);
   if (ws_bytes < V.end) return -7;
@@ -1078,9 +1083,15 @@ int32_t tchol_plan_query(int32_t op, int64_t n, int64_t nb, int32_t policy, uint
     return -1;
   if (n < 0 || n > INT32_MAX) return -2;
   if (!nb_ok(nb)) return -3;
+  const bool run_plan = run_policy(policy) && (op == TCHOL_OP_FACTOR || op == TCHOL_OP_FACTOR_SOLVE);
+  if (run_plan) policy = claim_policy(policy);
   if (!policy_ok(policy)) return -4;
   std::shared_ptr<const Plan> p;
-  if (op == TCHOL_OP_FACTOR_SOLVE) {
+  if (run_plan)
+    p = op == TCHOL_OP_FACTOR ? tchol::get_run_plan(op, n, nb, policy, seed)
+                              : tchol::get_run_merged_plan(n, nb, policy, seed, true);
+  if (p) {
+  } else if (op == TCHOL_OP_FACTOR_SOLVE) {
     std::vector<tchol::System> systems(1);
     systems[0].n = n;
     systems[0].nb = nb;

@@ -128,6 +128,9 @@ def main(argv=None):
         n, nb = args.n or 32768, args.nb or 512
         mixed = args.op == "mixed"
         A, rng = spd_inputs.spd_matrix_device(n, 2 if mixed else 1, 1e-4 if mixed else 1.0, device=dev)
+        # a factorization, alone or merged: the plan that an untraced launch runs
+        if args.op in ("factor", "merged"):
+            pol |= tc.PLAN_RUN
         # the mixed-precision factorization's DAG also holds the TRTRI tasks
         plan = tc.plan_query(tc.OP_MIXED_FACTOR if mixed else tc.OP_FACTOR, n, nb, pol)
         trace = torch.zeros(4 * plan["nitem"], dtype=torch.int64, device=dev)

@@ -53,3 +53,28 @@ def test_the_check_notices_missing_edges(checker, kind):
     """Without the edges into one kind of task the check must fail."""
     r = subprocess.run([checker, str(kind)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert r.returncode == 1 and "not ordered" in r.stdout
+
+
+def _query(op, n, nb, policy):
+    try:
+        return tc.plan_query(op, n, nb, policy)
+    except ImportError as e:  # library not built
+        pytest.skip(str(e))
+
+
+@pytest.mark.parametrize("policy", [tc.POLICY_LIST, tc.POLICY_RANK, tc.POLICY_FIFO, tc.POLICY_RANDOM])
+def test_query_of_the_run_plan(policy):
+    """PLAN_RUN: tiles of 128 in the factorization, the caller's in the solve."""
+    n, nb = 1600, 512
+    run = _query(tc.OP_FACTOR_SOLVE, n, nb, policy | tc.PLAN_RUN)
+    kinds = [tc.KIND_NAMES[k] for k in run["kind"]]
+    assert kinds.count("POTRF") == 13 and kinds.count("FTRSV") == 4 and kinds.count("GEMM4") > 0
+    assert sorted(set(run["item_task"])) == list(range(run["ntask"]))
+    factor = _query(tc.OP_FACTOR, n, nb, policy | tc.PLAN_RUN)
+    assert [tc.KIND_NAMES[k] for k in factor["kind"]].count("POTRF") == 13
+    # without the flag, and for the operations that have one plan only
+    assert [tc.KIND_NAMES[k] for k in _query(tc.OP_FACTOR, n, nb, policy)["kind"]].count("POTRF") == 4
+    with pytest.raises(tc.TcholError):
+        _query(tc.OP_SOLVE, n, nb, policy | tc.PLAN_RUN)
+    with pytest.raises(tc.TcholError):
+        _query(tc.OP_FACTOR, n, nb, -1)
