@@ -2046,7 +2046,6 @@ __device__ __forceinline__ int potrf_slabs(double* __restrict__ Akk, int64_t ld,
                   acc[rb][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[ks & 1][cb], fa[ks & 1][rb], acc[rb][cb], 0, 0, 2 /* neg B */);
             }
             __builtin_amdgcn_sched_barrier(0);
-            
           });
         };
         const int nch = c0 >> 4;  // even
@@ -3730,12 +3729,13 @@ __global__ void __launch_bounds__(NT, MODE >= 6 ? 2 : 1) tchol_persistent(KArgs 
           // before its right-hand sides are: it requests L, then waits.  L is
           // final from the start in a launch that only solves, and everywhere once
           // the last FTRSV is done (HDR_FWD); a diagonal tile's inverse once
-          // its TRTRI items have counted up its pool word.  Not at tiles of at
-          // most 128, whose strips read too little for it (n = 300 at 64: 266 us
-          // without, 275 with; n = 16384 at 512, solve alone: 2.50 ms without, 1.84 with).
+          // its TRTRI items have counted up its pool word.  Faster at every tile
+          // size: a solve alone takes, without / with it, 156 / 141 us at n = 300 and
+          // tiles of 64, 247 / 212 us at 1024 and 128, 631 / 475 us at 4096 and 256,
+          // 2.27 / 1.73 ms at 16384 and 512; merged at n = 300 and 64 247 us both ways.
           auto early_ok = [&]() __attribute__((always_inline)) {
             if constexpr (!SOLVE_KINDS || MODE == 4) return false;
-            if (!one_matrix || s_sys[SYS_WORDS * uniform_i(__builtin_amdgcn_readlane(dv, 7)) + 3] <= PSB) return false;
+            if (!one_matrix) return false;
             const int kd = uniform_i(__builtin_amdgcn_readlane(dv, 0)), pd = uniform_i(__builtin_amdgcn_readlane(dv, 4));
             bool ok = false;
             if (kd == TK_FGEMV) {
