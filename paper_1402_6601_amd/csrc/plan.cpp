@@ -887,7 +887,11 @@ std::shared_ptr<const Plan> get_batched_plan(const std::vector<System>& systems,
 // more often.  Factor and solve of 16 right-hand sides, caller's nb = 512, at
 // tiles of 128 / 256 / 512: n = 8192 5.6 / 9.1 / 10.8 ms, 12288 14.7 / 15.7 /
 // 17.0, 14336 22.1 / 22.2 / 21.0, 16384 31.6 / 30.2 / 28.2: the line lies below
-// the last two, and 256 is never the best.
+// the last two, and 256 is never the best.  Near the line the two sides meet
+// (4 right-hand sides, against the queried plan at the caller's 256 / 384 / 512):
+// n = 10001 9.7 against 12.4 / 14.2 / 14.8 ms, 11999 15.5 against 16.3 / 17.7 /
+// 18.4, 12288 15.2 against 15.9 / 14.8 / 17.5; factorization alone 14.8 against
+// 14.7 / 14.3 / 14.5.
 constexpr int64_t kRunTile = 128;
 constexpr int64_t kRunTileOrder = 12288;
 

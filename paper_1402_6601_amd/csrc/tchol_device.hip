@@ -1929,11 +1929,15 @@ __device__ __forceinline__ int potrf_tile(double* __restrict__ Akk, int64_t ld, 
 //     the matrix cores, and stores them from registers.
 // Slabs in LDS with one thread per row solving and storing (which this
 // replaces) spent as long outside the update as in it.  4096 systems of orders
-// 16 .. 512 in FP64, 4 right-hand sides: 4.75 -> 3.81 ms, mean POTRF 473 -> 347
-// us; of an order near 500 (1186 -> 914 us, two workgroups per compute unit)
-// now 680 in the update, whose panels are re-read from beyond the L2s, 120
-// in the diagonal blocks, 81 in the rows below.  Three stages instead of two
-// were slower (4.12 ms), as was swapping the halves of odd k-rows for them.
+// 16 .. 512 in FP64, 4 right-hand sides: kernel 4.75 -> 3.28 ms, mean POTRF 473
+// -> 295 us.  What is left is mostly the update, whose panels are re-read from
+// beyond the L2s (680 of 914 us at an order near 500 when the kernel took 3.81
+// ms; 120 in the diagonal blocks, 81 in the rows below).  Bound by registers
+// too: two workgroups per compute unit leave 256, and 85 (143 with FP32
+// storage) are spilled; keeping the four pivots' reciprocal roots of a quad
+// alive as well spilled 145 (211) and cost 0.5 ms (1.0).  Three stages instead
+// of two were slower (4.12 against 3.81 ms), as was swapping the halves of odd
+// k-rows for them.
 // With Bf the forward solve L y = b of nrhs <= 4 right-hand sides
 // (column-major at Bf, leading dimension ldbf) rides along: a panel's rows of
 // b, transposed, are one more row block for step 3 (wavefront 0), and the rows
