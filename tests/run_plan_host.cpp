@@ -239,6 +239,10 @@ int main(int argc, char** argv) {
         plans += 2;
       }
     }
+  // nothing to do: no merged plan to run, and a factorization without tasks
+  if (tchol::get_run_merged_plan(0, 512, TCHOL_POLICY_LIST, 0, true)) FAIL("a merged plan of order 0\n");
+  auto empty = tchol::get_run_plan(TCHOL_OP_FACTOR, 0, 512, TCHOL_POLICY_LIST, 0);
+  if (!empty || empty->ntask() != 0) FAIL("the factorization of order 0\n");
   std::printf("run plans: %d checked, %ld failures\n", plans, failures);
   return failures == 0 ? 0 : 1;
 }

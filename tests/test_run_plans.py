@@ -33,7 +33,8 @@ def checker(tmp_path_factory):
     if shutil.which("g++") is None:
         pytest.skip("needs g++")
     exe = str(tmp_path_factory.mktemp("run_plans") / "run_plan_host")
-    cmd = ["g++", "-std=c++17", "-O2", "-Wall", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-Wall", "-fno-omit-frame-pointer", "-fsanitize=address,undefined",
+           "-fno-sanitize-recover=undefined", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
            os.path.join(ROOT, "tests", "run_plan_host.cpp"), os.path.join(CSRC, "plan.cpp"), "-o", exe]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout[-4000:]
