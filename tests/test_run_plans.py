@@ -29,7 +29,7 @@ def test_workspace_of_an_empty_system(nb):
 
 
 @pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def host_check(tmp_path_factory):
     if shutil.which("g++") is None:
         pytest.skip("needs g++")
     exe = str(tmp_path_factory.mktemp("run_plans") / "run_plan_host")
@@ -41,18 +41,18 @@ def checker(tmp_path_factory):
     return exe
 
 
-def test_data_flow_claim_order_and_items(checker):
+def test_data_flow_claim_order_and_items(host_check):
     """Two tile sizes in one plan, merged updates, POTRF with its inverse, fine
     work items: conflicts ordered, claim orders topological, outputs covered."""
-    r = subprocess.run([checker], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    r = subprocess.run([host_check], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-4000:]
     assert r.stdout.rstrip().endswith(", 0 failures")
 
 
 @pytest.mark.parametrize("kind", [0, 1, 2, 3, 4, 5, 6, 7, 12, 19])
-def test_the_check_notices_missing_edges(checker, kind):
+def test_the_check_notices_missing_edges(host_check, kind):
     """Without the edges into one kind of task the check must fail."""
-    r = subprocess.run([checker, str(kind)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    r = subprocess.run([host_check, str(kind)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert r.returncode == 1 and "not ordered" in r.stdout
 
 
